@@ -266,7 +266,7 @@ hipError_t launch_reset_scalars(const LatView& v, double a, double p_a, const Of
 hipError_t launch_gather_scalars(const BatchRun* runs_dev, int nruns, DevScalars* out_dev,
                                  hipStream_t s);
 
-// ---- initial state and spectrum (kernels_init.hip) ------------------------
+// ---- initial state (kernels_init.hip) ----------------------------------------
 // Every site of buffer 0 = (phi0, pi0) less the state's offsets (the
 // remainders are 0 in FP32 storage with offsets phi0, pi0).
 hipError_t launch_fill_homogeneous(const LatView& v, const double* phi0, const double* pi0,
@@ -285,26 +285,64 @@ hipError_t launch_add_real(const LatView& v, const double2* cbuf, int field, dou
 // White noise of one field: phi_field (buffer 0) = base + amp (g - mean g).
 hipError_t launch_white(const LatView& v, double* gbuf, double* mean_dev, int field, double base,
                         double amp, uint64_t seed, hipStream_t s);
-// phi_sync of one field as the real part of cbuf.
-hipError_t launch_field_to_complex(const LatView& v, int field, double2* cbuf, hipStream_t s);
-// Workgroups used by the spectrum binning for side n.
-int spectrum_blocks(int n);
-// Shell sums of |F|^2 / n^6 of the transformed field; out3 = [k | P | count].
-hipError_t launch_spectrum_bins(int n, double L, const double2* cbuf, int nbins, double* part,
-                                double* out3, hipStream_t s);
 
-// ---- energy / number spectra (spectra.hip) ---------------------------------
-// m_eff^2 = lattice mean of d^2V/dphi_i^2 at the synchronised fields, per
-// field, into m2_dev (part: meff_partial_doubles(nf) doubles of scratch).
-size_t meff_partial_doubles(int nf);
-hipError_t launch_meff(const LatView& v, double* part, double* m2_dev, hipStream_t s);
-// The stored momenta of one field as the real part of cbuf.
-hipError_t launch_momentum_to_complex(const LatView& v, int field, double2* cbuf, hipStream_t s);
-// Binned field, energy and number spectra from the transforms F (field) and
-// P (momentum) of one field; out5 = [k | <|F|^2> | <rho> | <n> | count].
-int mode_spectra_blocks(int n);
-hipError_t launch_mode_spectra(const LatView& v, int field, const double2* F, const double2* P,
-                               int nbins, double* part, const double* m2_dev, double* out5,
-                               hipStream_t s);
+// ---- transforms (fft.hip) ---------------------------------------------------
+// Mixed-radix plan of one line of n values and the half-spectrum geometry
+// (see fft.h); m_*: division constants.
+struct FftPlan {
+  int n, nh, nhp;  // modes kept along x, and the row pitch
+  int nst, direct;  // stages; 1 if some factor is above 8
+  int cls, nt;      // kernel class (radices it holds) and threads
+  int radix[10], ns[10];
+  unsigned m_ns[10], m_nr[10];
+  unsigned m_n, m_nh, m_nhp, m_hy;
+};
+FftPlan fft_plan(int n);
+constexpr int kFftPerThread = 8;  // values a thread holds between stages
+int fft_column_lines_log2(const FftPlan& P);  // lines of a group of columns
+size_t fft_lds_bytes(int n, int lines);
+
+// Where a half spectrum (n planes of n nhp complex values) lies: planes
+// [0, z1) in piece 0, [z1, z2) in piece 1, the others in piece 2.  With sc,
+// pieces of pair sc->parity ^ 1: the lattice arrays that do not hold the
+// state; without, pair 0.
+struct ModeBuf {
+  void* seg[2][3];
+  double* part[2];  // rows of binning partials, same pairs
+  int z1, z2;
+  const DevScalars* sc;
+};
+
+// tw[m] = exp(-2 pi i m/n); ax[m] = 4 sin^2(pi m/n) (7-point stencil) or
+// cos(2 pi m/n) (any other member): what k_eff^2 is made of.
+hipError_t launch_fft_tables(int n, const Stencil& st, double2* tw, double* ax, hipStream_t s);
+// x pass of one field of the synchronised state (momentum: of its momenta)
+// less a constant: every mode but k = 0 is the field's.
+hipError_t launch_field_rows(const LatView& v, int field, int momentum, const FftPlan& P,
+                             const ModeBuf& B, const double2* tw, hipStream_t s);
+// In-place columns along y (axis 1) or z (axis 2).
+hipError_t launch_fft_columns(const FftPlan& P, const ModeBuf& B, const double2* tw, int axis,
+                              int inverse, hipStream_t s);
+
+// ---- field, energy and number spectra (spectra.hip) --------------------------
+// Bins a call fills: nbins, or as many as the lattice's modes reach.
+int spectrum_bins(int n, int nbins);
+int bin_rows_max(const FftPlan& P);  // most rows of partial bins a pass writes
+// m_eff^2 = lattice mean of d^2V/dphi_field^2 at the synchronised fields into
+// *m2_dev (part: meff_partial_doubles() doubles of scratch).
+size_t meff_partial_doubles();
+hipError_t launch_meff(const LatView& v, int field, double* part, double* m2_dev, hipStream_t s);
+// z pass and shell sums of |F|^2 / n^6; out3 = [k | P | count], nbe each.
+// `rows` workgroups, each writing 3 nbe partial sums.
+hipError_t launch_spectrum_bins(const LatView& v, const FftPlan& P, const ModeBuf& B, const double2* tw,
+                                const double* ax, int nbe, int rows, double* out3, hipStream_t s);
+// The same for the three spectra: the field's part (5 nbe partial sums a
+// row), then the momentum's (2 nbe), then the means; out5 = [k | <|F|^2> |
+// <rho> | <n> | count].
+hipError_t launch_mode_bins(const LatView& v, int momentum, const FftPlan& P, const ModeBuf& B,
+                            const double2* tw, const double* ax, int nbe, int rows, const double* m2_dev,
+                            hipStream_t s);
+hipError_t launch_mode_bins_finalize(const LatView& v, const ModeBuf& B, int nbe, int rows, double* out5,
+                                     hipStream_t s);
 
 }  // namespace symlat

@@ -1,4 +1,4 @@
-// Initial state and field spectrum on the device.
+// Initial state on the device.
 //
 // Random numbers: counter-based SplitMix64 (Steele, Lea & Flood, OOPSLA 2014:
 // the k-th output from a seed is the published finaliser applied to
@@ -246,76 +246,6 @@ __global__ void white_store_kernel(void* phi0, const double* g, const double* me
     phi[field_site(field, e, zs, n2)] = static_cast<T>(base + amp * (g[e] - mu));
 }
 
-template <typename T>
-__global__ void field_to_complex_kernel(const void* const phi_b0, const void* const phi_b1,
-                                        const void* const pi_b0, const void* const pi_b1,
-                                        const DevScalars* sc, size_t n3, size_t n2, int zs,
-                                        int field, double2* F) {
-  const int par = sc->parity;
-  const T* phi = static_cast<const T*>(par ? phi_b1 : phi_b0);
-  const T* pi = static_cast<const T*>(par ? pi_b1 : pi_b0);
-  const double c = sc->c_pend;
-  const double offp = sc->off_phi[field] + c * sc->off_pi[field];
-  const size_t stride = size_t(gridDim.x) * blockDim.x;
-  for (size_t e = size_t(blockIdx.x) * blockDim.x + threadIdx.x; e < n3; e += stride) {
-    const size_t d = field_site(field, e, zs, n2);
-    F[e] = make_double2(offp + fma(c, double(pi[d]), double(phi[d])), 0.0);
-  }
-}
-
-// Shell index of |n|^2 = m: round(|n|) half away from zero, in integers.
-__device__ __forceinline__ int shell_of(long long m) {
-  long long b = (long long)floor(sqrt(double(m)));
-  if (b * b > m) --b;
-  if ((b + 1) * (b + 1) <= m) ++b;
-  return int(m > b * b + b ? b + 1 : b);
-}
-
-__global__ __launch_bounds__(kBlock) void spectrum_bins_kernel(int n, const double2* __restrict__ F,
-                                                              int nbins, double inv_n6,
-                                                              double* part) {
-  extern __shared__ double sh[];  // [3][nbins]: sum |F|^2, sum |n|, count
-  for (int b = threadIdx.x; b < 3 * nbins; b += blockDim.x) sh[b] = 0.0;
-  __syncthreads();
-  const size_t n2 = size_t(n) * n, n3 = n2 * n;
-  const size_t stride = size_t(gridDim.x) * blockDim.x;
-  for (size_t e = size_t(blockIdx.x) * blockDim.x + threadIdx.x; e < n3; e += stride) {
-    int kx = int(e % n), ky = int((e / n) % n), kz = int(e / n2);
-    if (2 * kx >= n) kx -= n;
-    if (2 * ky >= n) ky -= n;
-    if (2 * kz >= n) kz -= n;
-    const long long m = (long long)kx * kx + (long long)ky * ky + (long long)kz * kz;
-    if (m == 0) continue;
-    const int b = shell_of(m);
-    if (b >= nbins) continue;
-    const double2 f = F[e];
-    atomicAdd(&sh[b], (f.x * f.x + f.y * f.y) * inv_n6);
-    atomicAdd(&sh[nbins + b], sqrt(double(m)));
-    atomicAdd(&sh[2 * nbins + b], 1.0);
-  }
-  __syncthreads();
-  double* out = part + size_t(blockIdx.x) * 3 * nbins;
-  for (int b = threadIdx.x; b < 3 * nbins; b += blockDim.x) out[b] = sh[b];
-}
-
-__global__ void spectrum_finalize_kernel(const double* part, int nblocks, int nbins, double L,
-                                         double* out3) {
-  const int b = blockIdx.x * blockDim.x + threadIdx.x;
-  if (b >= nbins) return;
-  KSum p{0.0, 0.0}, k{0.0, 0.0};
-  double cnt = 0.0;
-  for (int q = 0; q < nblocks; ++q) {
-    const double* r = part + size_t(q) * 3 * nbins;
-    kadd(p, r[b]);
-    kadd(k, r[nbins + b]);
-    cnt += r[2 * nbins + b];
-  }
-  const double P = p.s + p.c, K = k.s + k.c;
-  out3[b] = cnt > 0 ? 2.0 * M_PI * (K / cnt) / L : 0.0;
-  out3[nbins + b] = cnt > 0 ? P / cnt : 0.0;
-  out3[2 * nbins + b] = cnt;
-}
-
 int grid_for(size_t count) {
   size_t nb = (count + kBlock - 1) / kBlock;
   if (nb > 4096) nb = 4096;
@@ -410,38 +340,6 @@ hipError_t launch_white(const LatView& v, double* gbuf, double* mean_dev, int fi
   else
     hipLaunchKernelGGL(white_store_kernel<double>, dim3(grid_for(n3)), dim3(kBlock), 0, s,
                        v.phi[0], gbuf, mean_dev, n3, size_t(v.n) * v.n, v.zs, field, base, amp);
-  return hipGetLastError();
-}
-
-hipError_t launch_field_to_complex(const LatView& v, int field, double2* cbuf, hipStream_t s) {
-  const size_t n3 = size_t(v.n) * v.n * v.n;
-  if (v.prec == SL_FP32)
-    hipLaunchKernelGGL(field_to_complex_kernel<float>, dim3(grid_for(n3)), dim3(kBlock), 0, s,
-                       v.phi[0], v.phi[1], v.pi[0], v.pi[1], v.sc, n3, size_t(v.n) * v.n, v.zs,
-                       field, cbuf);
-  else
-    hipLaunchKernelGGL(field_to_complex_kernel<double>, dim3(grid_for(n3)), dim3(kBlock), 0, s,
-                       v.phi[0], v.phi[1], v.pi[0], v.pi[1], v.sc, n3, size_t(v.n) * v.n, v.zs,
-                       field, cbuf);
-  return hipGetLastError();
-}
-
-int spectrum_blocks(int n) {
-  const size_t n3 = size_t(n) * n * n;
-  const int nb = grid_for(n3);
-  return nb > 256 ? 256 : nb;
-}
-
-hipError_t launch_spectrum_bins(int n, double L, const double2* cbuf, int nbins, double* part,
-                                double* out3, hipStream_t s) {
-  const int nb = spectrum_blocks(n);
-  const double n3 = double(n) * n * n;
-  hipLaunchKernelGGL(spectrum_bins_kernel, dim3(nb), dim3(kBlock), size_t(3) * nbins * sizeof(double),
-                     s, n, cbuf, nbins, 1.0 / (n3 * n3), part);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(spectrum_finalize_kernel, dim3((nbins + 255) / 256), dim3(256), 0, s, part,
-                     nb, nbins, L, out3);
   return hipGetLastError();
 }
 

@@ -460,15 +460,102 @@ sl_status dft3(sl_lattice* L, double2* a, double2* b, double2* tw, int sign) {
 
 sl_status dft3(sl_lattice* L, FftScratch& S, int sign) { return dft3(L, S.a, S.b, S.tw, sign); }
 
-size_t spectrum_part_bytes(int n, int nbins) {
-  return size_t(spectrum_blocks(n)) * 3 * size_t(nbins) * sizeof(double);
-}
-
-// Scratch of one spectrum call: two transform buffers, the twiddles and the
-// binning partials (256-byte aligned).
+// Largest scratch a spectrum call may take from the static array: two complex
+// n^3 arrays, twiddles and 3 nbins binning sums of up to 256 workgroups.
 size_t spectrum_noalloc_bytes(int n, int nbins) {
   const size_t nn = size_t(n), n3 = nn * nn * nn;
-  return round256(2 * n3 * sizeof(double2) + nn * sizeof(double2)) + spectrum_part_bytes(n, nbins);
+  return round256(2 * n3 * sizeof(double2) + nn * sizeof(double2)) +
+         std::min<size_t>((n3 + kBlock - 1) / kBlock, 256) * 3 * size_t(nbins) * sizeof(double);
+}
+
+// Scratch of a spectrum call: the half spectrum and the binning partials in
+// the lattice's arrays that do not hold the state (the next stage pass
+// overwrites them), the tables and the m_eff^2 partials in the chaining
+// buffer, which is free between calls.  Nothing is allocated, except where
+// those arrays are too small: FP32 storage of one field at sides above about
+// 300, whose arrays are 16 n^2 bytes short and overflow into the partial-sum
+// buffer only up to there.
+struct SpecScratch {
+  FftPlan P;
+  ModeBuf B{};
+  int nbe = 0, rows = 0;
+  double2* tw = nullptr;
+  double* ax = nullptr;
+  double* mpart = nullptr;
+  double* m2 = nullptr;
+  void* owned = nullptr;
+  ~SpecScratch() {
+    if (owned) (void)hipFree(owned);
+  }
+};
+
+// Rows of partial bins that fit `bytes`, at most what a pass can use.
+int rows_in(const SpecScratch& S, size_t bytes, int per_row) {
+  const size_t r = bytes / (size_t(per_row) * S.nbe * sizeof(double));
+  return int(std::min<size_t>(r, size_t(bin_rows_max(S.P))));
+}
+
+sl_status spec_scratch(sl_lattice* L, int nbins, int per_row, unsigned char* fixed, size_t fixed_bytes,
+                       SpecScratch& S) {
+  const LatView& v = L->v;
+  const int n = v.n;
+  S.P = fft_plan(n);
+  S.nbe = spectrum_bins(n, nbins);
+  static_assert(kChainMaxTiles * 6 >= 3 * 1024 + 2 * 1024, "tables and m_eff^2 partials");
+  S.tw = reinterpret_cast<double2*>(v.partials1);
+  S.ax = v.partials1 + 2 * size_t(n);
+  S.mpart = S.ax + n;
+  S.m2 = L->sums_dev;
+  const size_t plane = size_t(n) * S.P.nhp * sizeof(double2), need = plane * n;
+  const int want = std::min(bin_rows_max(S.P), 64);
+  auto one_piece = [&](unsigned char* p, size_t bytes) {
+    S.B.sc = nullptr;
+    S.B.z1 = S.B.z2 = n;
+    S.B.seg[0][0] = p;
+    S.B.part[0] = reinterpret_cast<double*>(p + need);
+    S.rows = rows_in(S, bytes - need, per_row);
+  };
+  if (fixed) {
+    one_piece(fixed, fixed_bytes);
+    return SL_OK;
+  }
+  // pieces: the spare phi and pi arrays (one block when they are interleaved
+  // by plane), then the partial-sum buffer
+  const size_t arr = L->n3 * v.nf * L->elem;
+  const bool block = v.zs == 2 * v.nf;
+  const size_t cap[3] = {block ? 2 * arr : arr, block ? 0 : arr, partial_doubles() * sizeof(double)};
+  int zt[3], z = 0;
+  for (int q = 0; q < 3; ++q) {
+    zt[q] = int(std::min<size_t>(size_t(n - z), cap[q] / plane));
+    z += zt[q];
+  }
+  int best = 0;
+  size_t room = 0;
+  for (int q = 0; q < 3; ++q)
+    if (cap[q] - zt[q] * plane > room) {
+      room = cap[q] - zt[q] * plane;
+      best = q;
+    }
+  S.rows = rows_in(S, room, per_row);
+  if (z == n && S.rows >= want) {
+    S.B.sc = v.sc;
+    S.B.z1 = zt[0];
+    S.B.z2 = zt[0] + zt[1];
+    for (int k = 0; k < 2; ++k) {
+      S.B.seg[k][0] = v.phi[k];
+      S.B.seg[k][1] = v.pi[k];
+      S.B.seg[k][2] = v.partials;
+      S.B.part[k] = reinterpret_cast<double*>(static_cast<unsigned char*>(S.B.seg[k][best]) + zt[best] * plane);
+    }
+    return SL_OK;
+  }
+  const size_t bytes = need + size_t(bin_rows_max(S.P)) * per_row * S.nbe * sizeof(double);
+  if (hipMalloc(&S.owned, bytes) != hipSuccess) {
+    S.owned = nullptr;
+    return fail(SL_E_NOMEM, "cannot allocate transform scratch (%zu bytes)", bytes);
+  }
+  one_piece(static_cast<unsigned char*>(S.owned), bytes);
+  return SL_OK;
 }
 
 sl_status spectrum_check(sl_lattice* L, int field, int nbins, const double* k_out,
@@ -480,27 +567,31 @@ sl_status spectrum_check(sl_lattice* L, int field, int nbins, const double* k_ou
   return SL_OK;
 }
 
-// Field power spectrum with caller-provided device scratch: a, b (n^3
-// complex each), tw (n complex), part (spectrum_part_bytes).  Allocates no
-// device memory; synchronises the lattice's stream.
-sl_status spectrum_run(sl_lattice* L, int field, int nbins, double2* a, double2* b, double2* tw,
-                       double* part, double* k_out, double* p_out, int64_t* count_out) {
-  std::vector<double> host(size_t(3) * nbins);
-  hipError_t e = launch_field_to_complex(L->v, field, a, L->stream);
-  if (e == hipSuccess) {
-    const sl_status st = dft3(L, a, b, tw, -1);
-    if (st != SL_OK) return st;
-    e = launch_spectrum_bins(L->cfg.n, L->cfg.L, b, nbins, part, L->spec_dev, L->stream);
-  }
+// x and y passes of a field's (or its momenta's) transform into the scratch.
+hipError_t transform_rows(sl_lattice* L, int field, int momentum, const SpecScratch& S) {
+  hipError_t e = launch_field_rows(L->v, field, momentum, S.P, S.B, S.tw, L->stream);
+  if (e == hipSuccess) e = launch_fft_columns(S.P, S.B, S.tw, 1, 0, L->stream);
+  return e;
+}
+
+// Field power spectrum in the scratch S; synchronises the lattice's stream.
+sl_status spectrum_run(sl_lattice* L, int field, int nbins, const SpecScratch& S, double* k_out,
+                       double* p_out, int64_t* count_out) {
+  std::vector<double> host(size_t(3) * S.nbe);
+  hipError_t e = launch_fft_tables(L->cfg.n, L->v.st, S.tw, S.ax, L->stream);
+  if (e == hipSuccess) e = transform_rows(L, field, 0, S);
+  if (e == hipSuccess)
+    e = launch_spectrum_bins(L->v, S.P, S.B, S.tw, S.ax, S.nbe, S.rows, L->spec_dev, L->stream);
   if (e == hipSuccess)
     e = hipMemcpyAsync(host.data(), L->spec_dev, host.size() * sizeof(double), hipMemcpyDeviceToHost,
                        L->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(L->stream);
   if (e != hipSuccess) return fail(SL_E_DEVICE, "spectrum: %s", hipGetErrorString(e));
   for (int k = 0; k < nbins; ++k) {
-    k_out[k] = host[k];
-    p_out[k] = host[nbins + k];
-    count_out[k] = int64_t(host[2 * nbins + k]);
+    const bool own = k < S.nbe;  // no mode reaches the others
+    k_out[k] = own ? host[k] : 0.0;
+    p_out[k] = own ? host[S.nbe + k] : 0.0;
+    count_out[k] = own ? int64_t(host[2 * S.nbe + k]) : 0;
   }
   DevScalars Sc;
   return read_scalars(L, &Sc);
@@ -562,11 +653,10 @@ size_t sl_transient_bytes(const sl_config* cfg) {
   const size_t fft = 2 * n3 * sizeof(double2) + n * sizeof(double2);
   const size_t staging = 2 * nf * n3 * sizeof(double);               // set/get fields
   const size_t white = n3 * sizeof(double) + sizeof(double);         // white initial state
-  const size_t spectrum = fft + size_t(spectrum_blocks(cfg->n)) * 3 * kMaxBins * sizeof(double);
-  const size_t spectra = fft + n3 * sizeof(double2) +
-                         size_t(mode_spectra_blocks(cfg->n)) * 5 * kMaxBins * sizeof(double) +
-                         meff_partial_doubles(cfg->nfields) * sizeof(double) +
-                         (kMaxFields + 5 * kMaxBins) * sizeof(double);
+  const size_t blocks = std::min<size_t>((n3 + kBlock - 1) / kBlock, 256);
+  const size_t spectrum = fft + blocks * 3 * kMaxBins * sizeof(double);
+  const size_t spectra = fft + n3 * sizeof(double2) + blocks * 5 * kMaxBins * sizeof(double) +
+                         256 * 2 * nf * sizeof(double) + (kMaxFields + 5 * kMaxBins) * sizeof(double);
   return std::max({fft, staging, white, spectrum, spectra});
 }
 
@@ -1141,22 +1231,16 @@ sl_status sl_spectrum(sl_lattice* L, int32_t field, int32_t nbins, double* k_out
                       int64_t* count_out) {
   sl_status st = spectrum_check(L, field, nbins, k_out, p_out, count_out);
   if (st != SL_OK) return st;
-  FftScratch S;
-  st = fft_alloc(L, S);
+  SpecScratch S;
+  st = spec_scratch(L, nbins, 3, nullptr, 0, S);
   if (st != SL_OK) return st;
-  double* part = nullptr;
-  if (hipMalloc(&part, spectrum_part_bytes(L->cfg.n, nbins)) != hipSuccess)
-    return fail(SL_E_NOMEM, "cannot allocate spectrum partials");
-  st = spectrum_run(L, field, nbins, S.a, S.b, S.tw, part, k_out, p_out, count_out);
-  (void)hipFree(part);
-  return st;
+  return spectrum_run(L, field, nbins, S, k_out, p_out, count_out);
 }
 
 sl_status sl_spectrum_noalloc(sl_lattice* L, int32_t field, int32_t nbins, double* k_out,
                               double* p_out, int64_t* count_out) {
   sl_status st = spectrum_check(L, field, nbins, k_out, p_out, count_out);
   if (st != SL_OK) return st;
-  const size_t n = size_t(L->cfg.n), n3 = n * n * n;
   const size_t need = spectrum_noalloc_bytes(L->cfg.n, nbins);
   if (need > kNoAllocScratchBytes)
     return fail(SL_E_INVALID,
@@ -1166,13 +1250,12 @@ sl_status sl_spectrum_noalloc(sl_lattice* L, int32_t field, int32_t nbins, doubl
   unsigned char* base = nullptr;
   st = noalloc_scratch(L->device, &base);
   if (st != SL_OK) return st;
-  // layout: transform buffers a, b (n^3 complex each), twiddles (n), then
-  // the binning partials; every kernel writes its part before reading it
-  double2* a = reinterpret_cast<double2*>(base);
-  double2* b = a + n3;
-  double2* tw = b + n3;
-  double* part = reinterpret_cast<double*>(base + round256(2 * n3 * sizeof(double2) + n * sizeof(double2)));
-  return spectrum_run(L, field, nbins, a, b, tw, part, k_out, p_out, count_out);
+  // the half spectrum, then the binning partials; every kernel writes its
+  // part before reading it
+  SpecScratch S;
+  st = spec_scratch(L, nbins, 3, base, kNoAllocScratchBytes, S);
+  if (st != SL_OK) return st;
+  return spectrum_run(L, field, nbins, S, k_out, p_out, count_out);
 }
 
 sl_status sl_spectra(sl_lattice* L, int32_t field, int32_t nbins, double* k_out, double* pf_out,
@@ -1183,64 +1266,33 @@ sl_status sl_spectra(sl_lattice* L, int32_t field, int32_t nbins, double* k_out,
   if (nbins < 1 || nbins > kMaxBins) return fail(SL_E_INVALID, "nbins must be in [1, %d]", kMaxBins);
   if (!k_out || !pf_out || !pe_out || !pn_out || !count_out)
     return fail(SL_E_INVALID, "output array is NULL");
-  FftScratch S;
-  st = fft_alloc(L, S);
+  SpecScratch S;
+  st = spec_scratch(L, nbins, 7, nullptr, 0, S);  // 5 sums of the field's pass, 2 of the momentum's
   if (st != SL_OK) return st;
-  const int nb = mode_spectra_blocks(L->cfg.n);
-  const size_t mparts = meff_partial_doubles(L->cfg.nfields);
-  double* part = nullptr;
-  double* mpart = nullptr;
-  double* m2 = nullptr;
-  double* out5 = nullptr;
-  double2* F = nullptr;
-  auto release = [&]() {
-    for (void* p : {static_cast<void*>(part), static_cast<void*>(mpart), static_cast<void*>(m2),
-                    static_cast<void*>(out5), static_cast<void*>(F)})
-      if (p) (void)hipFree(p);
-  };
-  if (hipMalloc(&part, size_t(nb) * 5 * nbins * sizeof(double)) != hipSuccess ||
-      hipMalloc(&mpart, mparts * sizeof(double)) != hipSuccess ||
-      hipMalloc(&m2, kMaxFields * sizeof(double)) != hipSuccess ||
-      hipMalloc(&out5, size_t(5) * nbins * sizeof(double)) != hipSuccess ||
-      hipMalloc(&F, L->n3 * sizeof(double2)) != hipSuccess) {
-    release();
-    return fail(SL_E_NOMEM, "cannot allocate spectrum scratch");
+  std::vector<double> host(size_t(5) * S.nbe);
+  double m2h = 0.0;
+  hipError_t e = launch_fft_tables(L->cfg.n, L->v.st, S.tw, S.ax, L->stream);
+  if (e == hipSuccess) e = launch_meff(L->v, field, S.mpart, S.m2, L->stream);
+  for (int momentum = 0; momentum < 2; ++momentum) {
+    if (e == hipSuccess) e = transform_rows(L, field, momentum, S);
+    if (e == hipSuccess)
+      e = launch_mode_bins(L->v, momentum, S.P, S.B, S.tw, S.ax, S.nbe, S.rows, S.m2, L->stream);
   }
-  std::vector<double> host(size_t(5) * nbins);
-  double m2h[kMaxFields] = {0};
-  hipError_t e = launch_meff(L->v, mpart, m2, L->stream);
-  if (e == hipSuccess) e = launch_field_to_complex(L->v, field, S.a, L->stream);
-  if (e == hipSuccess) {
-    st = dft3(L, S, -1);
-    if (st != SL_OK) {
-      release();
-      return st;
-    }
-    e = hipMemcpyAsync(F, S.b, L->n3 * sizeof(double2), hipMemcpyDeviceToDevice, L->stream);
-  }
-  if (e == hipSuccess) e = launch_momentum_to_complex(L->v, field, S.a, L->stream);
-  if (e == hipSuccess) {
-    st = dft3(L, S, -1);
-    if (st != SL_OK) {
-      release();
-      return st;
-    }
-    e = launch_mode_spectra(L->v, field, F, S.b, nbins, part, m2, out5, L->stream);
-  }
+  if (e == hipSuccess) e = launch_mode_bins_finalize(L->v, S.B, S.nbe, S.rows, L->spec_dev, L->stream);
   if (e == hipSuccess)
-    e = hipMemcpyAsync(host.data(), out5, host.size() * sizeof(double), hipMemcpyDeviceToHost, L->stream);
-  if (e == hipSuccess) e = hipMemcpyAsync(m2h, m2, sizeof m2h, hipMemcpyDeviceToHost, L->stream);
+    e = hipMemcpyAsync(host.data(), L->spec_dev, host.size() * sizeof(double), hipMemcpyDeviceToHost, L->stream);
+  if (e == hipSuccess) e = hipMemcpyAsync(&m2h, S.m2, sizeof m2h, hipMemcpyDeviceToHost, L->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(L->stream);
-  release();
   if (e != hipSuccess) return fail(SL_E_DEVICE, "spectra: %s", hipGetErrorString(e));
   for (int b = 0; b < nbins; ++b) {
-    k_out[b] = host[b];
-    pf_out[b] = host[nbins + b];
-    pe_out[b] = host[2 * nbins + b];
-    pn_out[b] = host[3 * nbins + b];
-    count_out[b] = int64_t(host[4 * nbins + b]);
+    const bool own = b < S.nbe;  // no mode reaches the others
+    k_out[b] = own ? host[b] : 0.0;
+    pf_out[b] = own ? host[S.nbe + b] : 0.0;
+    pe_out[b] = own ? host[2 * S.nbe + b] : 0.0;
+    pn_out[b] = own ? host[3 * S.nbe + b] : 0.0;
+    count_out[b] = own ? int64_t(host[4 * S.nbe + b]) : 0;
   }
-  if (m2eff_out) *m2eff_out = m2h[field];
+  if (m2eff_out) *m2eff_out = m2h;
   DevScalars Sc;
   return read_scalars(L, &Sc);
 }
