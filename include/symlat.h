@@ -142,9 +142,10 @@ sl_status sl_lattice_create(const sl_config* cfg, void* hip_stream, sl_lattice**
  * handle zero-fills them at creation, uses them until sl_lattice_destroy and
  * never frees them; the caller keeps them alive that long and touches them
  * only between synchronising calls.  Which buffer holds the state alternates
- * with the stages, and in FP32 storage the arrays hold each field's and
- * momentum's remainder around a homogeneous FP64 offset the handle keeps:
- * read the state with sl_get_fields.  The small buffers (partial
+ * with the stages (the other one is working memory: the spectra and the
+ * initial states transform in it), and in FP32 storage the arrays hold each
+ * field's and momentum's remainder around a homogeneous FP64 offset the
+ * handle keeps: read the state with sl_get_fields.  The small buffers (partial
  * sums, scalars) are still the handle's.  SL_E_INVALID if an array is NULL,
  * misaligned, not device memory of this device, shorter than needed inside
  * its allocation, or overlaps another.  sl_footprint_bytes still counts the
@@ -225,11 +226,11 @@ sl_status sl_spectrum(sl_lattice* lat, int32_t field, int32_t nbins,
 
 /* sl_spectrum for callers that cannot allocate device memory (code under
  * HIP graph capture, tight serving loops, harnesses that forbid
- * hipMalloc): the same kernels and outputs, with the transform buffers and
+ * hipMalloc): the same kernels and outputs, with the half spectrum and the
  * binning partials in a library-owned static device array of 32 MiB per
- * GPU (held until the process ends) instead of per-call allocations.
- * Accepts lattices whose scratch fits it: 32 n^3 + 16 n bytes of transform
- * buffers and twiddles (rounded up to 256) plus 24 nbins m bytes of binning
+ * GPU (held until the process ends).
+ * Accepts lattices for which that array holds two complex n^3 arrays: 32 n^3
+ * + 16 n bytes (rounded up to 256) plus 24 nbins m bytes of binning
  * partials, m = min(ceil(n^3 / 256), 256) -- e.g. n <= 86 with any nbins,
  * n = 96 with up to 853 bins, n <= 101 with a few bins.  Every call on one GPU shares that array, so calls that
  * overlap on one GPU (two threads, or two streams without an ordering
@@ -300,10 +301,11 @@ sl_status sl_synchronize(sl_lattice* lat);
 
 /* Device bytes a lattice of this configuration holds from creation to
  * destruction (0 if invalid); sl_set_history adds 32 bytes per record.
- * sl_transient_bytes: the most any single call on such a lattice allocates
- * on top while it runs and frees before returning (vacuum or white initial
- * state, sl_set_fields / sl_get_fields staging, sl_spectrum, sl_spectra);
- * 0 if invalid.  Admission keeps footprint + transient free. */
+ * sl_transient_bytes: an upper bound of what any single call on such a
+ * lattice allocates on top while it runs and frees before returning
+ * (sl_set_fields / sl_get_fields staging; initial states and spectra work in
+ * the field arrays that do not hold the state and allocate only where those
+ * are too small, in FP32 storage of one field); 0 if invalid.  Admission keeps footprint + transient free. */
 size_t sl_footprint_bytes(const sl_config* cfg);
 size_t sl_transient_bytes(const sl_config* cfg);
 
@@ -475,8 +477,10 @@ sl_status sl_hbm_copy_bench(size_t bytes, int32_t iters, double* gbs);
 typedef struct sl_linear sl_linear;
 
 /* Create a handle for cfg (precision must be SL_FP64, nfields <= 4); the
- * stream is as for sl_lattice_create.  Device memory: 4 nfields n^3
- * complex modes plus transform scratch, and (2 nfields)^2 doubles per
+ * stream is as for sl_lattice_create.  Device memory: the modes with
+ * kx <= n/2 of nfields fields and momenta (2 nfields n^2 (n/2 + 1) complex
+ * values, rows padded to 8) and one such array of transform scratch, a copy
+ * of the host fields (2 nfields n^3 doubles), and (2 nfields)^2 doubles per
  * mode class (C(n/2 + 3, 3) classes).  SL_E_INVALID for a bad config. */
 sl_status sl_linear_create(const sl_config* cfg, void* hip_stream, sl_linear** out);
 sl_status sl_linear_destroy(sl_linear* lin);

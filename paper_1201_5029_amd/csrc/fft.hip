@@ -7,10 +7,6 @@ namespace symlat {
 
 namespace {
 
-// Workgroups of an axis pass: enough for every resident slot a few times
-// over; the groups of lines are dealt out in a loop.
-constexpr int kFftGridMax = 4096;
-
 __global__ void fft_tables_kernel(int n, Stencil st, double2* tw, double* ax) {
   const int m = blockIdx.x * blockDim.x + threadIdx.x;
   if (m < n) {
@@ -59,6 +55,21 @@ struct LatticeRows {
   }
 };
 
+// Rows of a plain real array [z][y][x] less a value in device memory.
+struct ArrayRows {
+  const double* r;
+  const double* shift;
+  struct View {
+    const double* r;
+    double shift;
+    size_t n;
+    __device__ __forceinline__ double operator()(int z, int y, int x) const {
+      return r[(size_t(z) * n + y) * n + x] - shift;
+    }
+  };
+  __device__ View view(int n) const { return View{r, *shift, size_t(n)}; }
+};
+
 // Forward x pass: pairs of real rows of `src` into half-spectrum rows.
 template <int NT, int CLS, class Src>
 __global__ __launch_bounds__(NT, NT == 256 ? 3 : 4) void r2c_rows_kernel(FftPlan P, Src src, ModeBuf B,
@@ -93,10 +104,77 @@ __global__ __launch_bounds__(NT, NT == 256 ? 3 : 4) void r2c_rows_kernel(FftPlan
   }
 }
 
-// Complex columns along y (axis 1) or z (axis 2), in place.  The inverse
-// exchanges real and imaginary parts on the way in and out.
+// Field i of a lattice's buffer 0 as the target of an inverse transform.
+template <typename T>
+struct LatticeSink {
+  void* phi;
+  void* pi;
+  int zs, field;
+  double base, pi_value;
+  __device__ __forceinline__ void put(int n, int z, int y, int x, double v) const {
+    const size_t o = ((size_t(z) * zs + field) * n + y) * n + x;
+    static_cast<T*>(phi)[o] = static_cast<T>(base + v);
+    static_cast<T*>(pi)[o] = static_cast<T>(pi_value);
+  }
+};
+
+// A plain real array [z][y][x] = scale * transform + *add (device memory).
+struct ArraySink {
+  double* r;
+  double scale;
+  const double* add;
+  __device__ __forceinline__ void put(int n, int z, int y, int x, double v) const {
+    r[(size_t(z) * n + y) * n + x] = fma(v, scale, *add);
+  }
+};
+
+// Inverse x pass: half-spectrum rows A, B of two neighbouring rows as the
+// complex row A + i B, whose inverse transform holds one row in its real and
+// the other in its imaginary part.  Z_k for k > n/2 is conj(A_{n-k}) +
+// i conj(B_{n-k}).  Real and imaginary parts exchanged, as in the columns.
+template <int NT, int CLS, class Sink>
+__global__ __launch_bounds__(NT, NT == 256 ? 3 : 4) void c2r_rows_kernel(FftPlan P, ModeBuf B, Sink sink,
+                                                      const double2* __restrict__ twg, int lines,
+                                                      int npairs) {
+  extern __shared__ double2 smem[];
+  const int n = P.n, hy = (n + 1) / 2;
+  double2* tw = smem;
+  double2* buf = smem + n;
+  for (int i = int(threadIdx.x); i < n; i += NT) tw[i] = twg[i];
+  const Modes in = modes_of(B, P);
+  const RowMap M{n};
+  __syncthreads();
+  for (int g0 = int(blockIdx.x) * lines; g0 < npairs; g0 += int(gridDim.x) * lines) {
+    const int cnt = min(lines, npairs - g0);
+    auto ld = [&](int l, int e) {
+      const int z = div_magic(g0 + l, P.m_hy), y = 2 * (g0 + l - z * hy);
+      const bool up = 2 * e > n;
+      const int k = up ? n - e : e;
+      const double2* row = in.at(z) + size_t(y) * P.nhp + k;
+      double2 a = row[0], b = y + 1 < n ? row[P.nhp] : make_double2(0.0, 0.0);
+      if (k == 0 || 2 * k == n) a.y = b.y = 0.0;  // real rows: rounding only
+      if (up) {
+        a.y = -a.y;
+        b.y = -b.y;
+      }
+      return make_double2(a.y + b.x, a.x - b.y);
+    };
+    auto st = [&](int l, int e, double2 v) {
+      const int z = div_magic(g0 + l, P.m_hy), y = 2 * (g0 + l - z * hy);
+      sink.put(n, z, y, e, v.y);
+      if (y + 1 < n) sink.put(n, z, y + 1, e, v.x);
+    };
+    fft_lines<NT, CLS, false>(P, M, cnt, buf, tw, ld, st);
+    __syncthreads();
+  }
+}
+
+// Complex columns along y (axis 1) or z (axis 2), from I to O (the same
+// buffer: in place).  The inverse exchanges real and imaginary parts on the
+// way in and out.
 template <int NT, int CLS>
-__global__ __launch_bounds__(NT, NT == 256 ? 3 : 4) void fft_columns_kernel(FftPlan P, ModeBuf B,
+__global__ __launch_bounds__(NT, NT == 256 ? 3 : 4) void fft_columns_kernel(FftPlan P, ModeBuf I,
+                                                         ModeBuf O,
                                                          const double2* __restrict__ twg, int lg,
                                                          int axis, int inverse) {
   extern __shared__ double2 smem[];
@@ -104,7 +182,7 @@ __global__ __launch_bounds__(NT, NT == 256 ? 3 : 4) void fft_columns_kernel(FftP
   double2* tw = smem;
   double2* buf = smem + n;
   for (int i = int(threadIdx.x); i < n; i += NT) tw[i] = twg[i];
-  const Modes m = modes_of(B, P);
+  const Modes in = modes_of(I, P), out = modes_of(O, P);
   const ColMap M{lg};
   __syncthreads();
   for (int g0 = int(blockIdx.x) * L; g0 < total; g0 += int(gridDim.x) * L) {
@@ -113,14 +191,14 @@ __global__ __launch_bounds__(NT, NT == 256 ? 3 : 4) void fft_columns_kernel(FftP
     const bool own = id < total;
     const int idc = own ? id : total - 1;
     const int z = div_magic(idc, P.m_nhp), x = idc - z * P.nhp;  // (z, kx) of a y line
-    double2* ycol = m.at(axis == 1 ? z : 0) + x;
-    auto at = [&](int e) { return axis == 1 ? ycol + size_t(e) * P.nhp : m.at(e) + idc; };
+    const double2* yin = in.at(axis == 1 ? z : 0) + x;
+    double2* yout = out.at(axis == 1 ? z : 0) + x;
     auto ld = [&](int, int e) {
-      const double2 v = *at(e);
+      const double2 v = axis == 1 ? yin[size_t(e) * P.nhp] : in.at(e)[idc];
       return inverse ? make_double2(v.y, v.x) : v;
     };
     auto st = [&](int, int e, double2 v) {
-      if (own) *at(e) = inverse ? make_double2(v.y, v.x) : v;
+      if (own) (axis == 1 ? yout + size_t(e) * P.nhp : out.at(e) + idc)[0] = inverse ? make_double2(v.y, v.x) : v;
     };
     fft_lines<NT, CLS, false>(P, M, L, buf, tw, ld, st);
     __syncthreads();
@@ -194,19 +272,36 @@ hipError_t launch_fft_tables(int n, const Stencil& st, double2* tw, double* ax, 
 
 namespace {
 
+// Groups of pairs of rows: small lattices take groups as small as it takes to
+// reach every CU.
+int row_lines(const FftPlan& P, int npairs) {
+  int lines = P.nt * kFftPerThread / P.n;
+  while (lines > 1 && npairs / lines < 256) lines = (lines + 1) / 2;
+  return lines;
+}
+
 template <class Src>
 hipError_t launch_r2c(const FftPlan& P, const Src& src, const ModeBuf& B, const double2* tw,
                       hipStream_t s) {
-  const int n = P.n, npairs = n * ((n + 1) / 2);
-  int lines = P.nt * kFftPerThread / n;
-  // small lattices: groups as small as it takes to reach every CU
-  while (lines > 1 && npairs / lines < 256) lines = (lines + 1) / 2;
+  const int n = P.n, npairs = n * ((n + 1) / 2), lines = row_lines(P, npairs);
   const int groups = (npairs + lines - 1) / lines;
   const dim3 grid(groups < kFftGridMax ? groups : kFftGridMax);
   const size_t lds = fft_lds_bytes(n, lines);
 #define R2C_LAUNCH(NT, CLS) return fft_launch(r2c_rows_kernel<NT, CLS, Src>, grid, NT, lds, s, P, src, B, tw, lines, npairs)
   FFT_DISPATCH(P, R2C_LAUNCH);
 #undef R2C_LAUNCH
+}
+
+template <class Sink>
+hipError_t launch_c2r(const FftPlan& P, const ModeBuf& B, const Sink& sink, const double2* tw,
+                      hipStream_t s) {
+  const int n = P.n, npairs = n * ((n + 1) / 2), lines = row_lines(P, npairs);
+  const int groups = (npairs + lines - 1) / lines;
+  const dim3 grid(groups < kFftGridMax ? groups : kFftGridMax);
+  const size_t lds = fft_lds_bytes(n, lines);
+#define C2R_LAUNCH(NT, CLS) return fft_launch(c2r_rows_kernel<NT, CLS, Sink>, grid, NT, lds, s, P, B, sink, tw, lines, npairs)
+  FFT_DISPATCH(P, C2R_LAUNCH);
+#undef C2R_LAUNCH
 }
 
 template <typename T>
@@ -232,14 +327,31 @@ hipError_t launch_field_rows(const LatView& v, int field, int momentum, const Ff
                            : r2c_lattice<double>(v, field, momentum, P, B, tw, s);
 }
 
-hipError_t launch_fft_columns(const FftPlan& P, const ModeBuf& B, const double2* tw, int axis,
-                              int inverse, hipStream_t s) {
+hipError_t launch_fft_columns(const FftPlan& P, const ModeBuf& I, const ModeBuf& O, const double2* tw,
+                              int axis, int inverse, hipStream_t s) {
   const int n = P.n, lg = fft_column_lines_log2(P), L = 1 << lg, groups = (n * P.nhp + L - 1) / L;
   const dim3 grid(groups < kFftGridMax ? groups : kFftGridMax);
   const size_t lds = fft_lds_bytes(n, L);
-#define COL_LAUNCH(NT, CLS) return fft_launch(fft_columns_kernel<NT, CLS>, grid, NT, lds, s, P, B, tw, lg, axis, inverse)
+#define COL_LAUNCH(NT, CLS) return fft_launch(fft_columns_kernel<NT, CLS>, grid, NT, lds, s, P, I, O, tw, lg, axis, inverse)
   FFT_DISPATCH(P, COL_LAUNCH);
 #undef COL_LAUNCH
+}
+
+hipError_t launch_rows_to_field(const LatView& v, int field, double base, double pi_value, const FftPlan& P,
+                                const ModeBuf& B, const double2* tw, hipStream_t s) {
+  if (v.prec == SL_FP32)
+    return launch_c2r(P, B, LatticeSink<float>{v.phi[0], v.pi[0], v.zs, field, base, pi_value}, tw, s);
+  return launch_c2r(P, B, LatticeSink<double>{v.phi[0], v.pi[0], v.zs, field, base, pi_value}, tw, s);
+}
+
+hipError_t launch_array_rows(const double* r, const double* shift, const FftPlan& P, const ModeBuf& B,
+                             const double2* tw, hipStream_t s) {
+  return launch_r2c(P, ArrayRows{r, shift}, B, tw, s);
+}
+
+hipError_t launch_rows_to_array(double* r, double scale, const double* add, const FftPlan& P,
+                                const ModeBuf& B, const double2* tw, hipStream_t s) {
+  return launch_c2r(P, B, ArraySink{r, scale, add}, tw, s);
 }
 
 }  // namespace symlat

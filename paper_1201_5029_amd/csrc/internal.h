@@ -271,18 +271,8 @@ hipError_t launch_gather_scalars(const BatchRun* runs_dev, int nruns, DevScalars
 // remainders are 0 in FP32 storage with offsets phi0, pi0).
 hipError_t launch_fill_homogeneous(const LatView& v, const double* phi0, const double* pi0,
                                    const Offsets& off, hipStream_t s);
-// Vacuum k-space amplitudes of one field into cbuf (complex FP64, n^3).
-hipError_t launch_vacuum_modes(const LatView& v, double2* cbuf, int field, double m2eff,
-                               double amp, uint64_t seed, hipStream_t s);
-// Twiddle table tw[m] = exp(sign 2 pi i m / n).
-hipError_t launch_twiddles(int n, int sign, double2* tw, hipStream_t s);
-// One 1-D DFT pass along axis (0 = x, 1 = y, 2 = z) with twiddle table tw.
-hipError_t launch_dft_axis(int n, const double2* in, double2* out, const double2* tw, int axis,
-                           hipStream_t s);
-// phi_field (buffer 0) = base + scale * Re(cbuf), rounded to storage precision.
-hipError_t launch_add_real(const LatView& v, const double2* cbuf, int field, double base,
-                           double scale, hipStream_t s);
-// White noise of one field: phi_field (buffer 0) = base + amp (g - mean g).
+// White noise of one field: phi_field (buffer 0) = base + amp (g - mean g);
+// gbuf: n^3 doubles of scratch.
 hipError_t launch_white(const LatView& v, double* gbuf, double* mean_dev, int field, double base,
                         double amp, uint64_t seed, hipStream_t s);
 
@@ -298,6 +288,9 @@ struct FftPlan {
   unsigned m_n, m_nh, m_nhp, m_hy;
 };
 FftPlan fft_plan(int n);
+// Workgroups of an axis pass at most (a few rounds of resident ones); the
+// groups of lines are dealt out in a loop.
+constexpr int kFftGridMax = 4096;
 constexpr int kFftPerThread = 8;  // values a thread holds between stages
 int fft_column_lines_log2(const FftPlan& P);  // lines of a group of columns
 size_t fft_lds_bytes(int n, int lines);
@@ -320,9 +313,24 @@ hipError_t launch_fft_tables(int n, const Stencil& st, double2* tw, double* ax, 
 // less a constant: every mode but k = 0 is the field's.
 hipError_t launch_field_rows(const LatView& v, int field, int momentum, const FftPlan& P,
                              const ModeBuf& B, const double2* tw, hipStream_t s);
-// In-place columns along y (axis 1) or z (axis 2).
-hipError_t launch_fft_columns(const FftPlan& P, const ModeBuf& B, const double2* tw, int axis,
-                              int inverse, hipStream_t s);
+// Columns along y (axis 1) or z (axis 2), from I to O (or in place).
+hipError_t launch_fft_columns(const FftPlan& P, const ModeBuf& I, const ModeBuf& O, const double2* tw,
+                              int axis, int inverse, hipStream_t s);
+
+// Half spectrum to field i of buffer 0: phi = base + its inverse transform
+// (last pass; the y and z passes come first), pi = pi_value everywhere.
+hipError_t launch_rows_to_field(const LatView& v, int field, double base, double pi_value, const FftPlan& P,
+                                const ModeBuf& B, const double2* tw, hipStream_t s);
+// x passes of a plain real array [z][y][x]: its transform less *shift, and
+// scale * (inverse transform) + *add (shift and add in device memory).
+hipError_t launch_array_rows(const double* r, const double* shift, const FftPlan& P, const ModeBuf& B,
+                             const double2* tw, hipStream_t s);
+hipError_t launch_rows_to_array(double* r, double scale, const double* add, const FftPlan& P,
+                                const ModeBuf& B, const double2* tw, hipStream_t s);
+// Vacuum modes of one field and their inverse z pass (kernels_init.hip).
+hipError_t launch_vacuum_columns(const LatView& v, int field, double m2eff, double amp, uint64_t seed,
+                                 const FftPlan& P, const ModeBuf& B, const double2* tw,
+                                 const double* ax, hipStream_t s);
 
 // ---- field, energy and number spectra (spectra.hip) --------------------------
 // Bins a call fills: nbins, or as many as the lattice's modes reach.

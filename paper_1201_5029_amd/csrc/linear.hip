@@ -34,7 +34,7 @@
 #include <string>
 #include <vector>
 
-#include "device.h"
+#include "fft.h"
 #include "timing.h"
 
 namespace symlat {
@@ -335,59 +335,72 @@ __global__ __launch_bounds__(kBlock) void lin_growth_kernel(double* __restrict__
     }
 }
 
-// Every Fourier mode times its class's M: (dPhi, dPi) <- M (dPhi, dPi).
+// Every Fourier mode with kx <= n/2 times its class's M: (dPhi, dPi) <-
+// M (dPhi, dPi); the conjugate modes follow.  Bound by the modes (read and
+// written once); M comes from the caches.
 template <int NF>
 __global__ __launch_bounds__(kBlock) void lin_apply_kernel(double2* __restrict__ dphi,
                                                            double2* __restrict__ dpi,
-                                                           const double* __restrict__ M, int n) {
+                                                           const double* __restrict__ M, FftPlan P,
+                                                           size_t stride) {
   constexpr int R = 2 * NF;
-  const size_t n2 = size_t(n) * n, n3 = n2 * n;
-  const size_t stride = size_t(gridDim.x) * blockDim.x;
-  for (size_t e = size_t(blockIdx.x) * blockDim.x + threadIdx.x; e < n3; e += stride) {
-    const int x = int(e % n), y = int((e / n) % n), z = int(e / n2);
-    const double* m = M + class_of_mode(z, y, x, n) * R * R;
-    double2 u[R];
+  const int n = P.n, id = int(blockIdx.x) * kBlock + int(threadIdx.x), z = int(blockIdx.y);
+  const int y = int(unsigned(id) / unsigned(P.nhp)), x = id - y * P.nhp;
+  if (y >= n || x >= P.nh) return;
+  const size_t e = size_t(z) * n * P.nhp + id;
+  const double* m = M + class_of_mode(z, y, x, n) * R * R;
+  double2 u[R];
 #pragma unroll
-    for (int i = 0; i < NF; ++i) {
-      u[i] = dphi[i * n3 + e];
-      u[NF + i] = dpi[i * n3 + e];
+  for (int i = 0; i < NF; ++i) {
+    u[i] = dphi[i * stride + e];
+    u[NF + i] = dpi[i * stride + e];
+  }
+  double2 v[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) v[r] = make_double2(0.0, 0.0);
+#pragma unroll
+  for (int col = 0; col < R; ++col)
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const double w = m[col * R + r];
+      v[r].x = fma(w, u[col].x, v[r].x);
+      v[r].y = fma(w, u[col].y, v[r].y);
     }
-    double2 v[R];
 #pragma unroll
-    for (int r = 0; r < R; ++r) v[r] = make_double2(0.0, 0.0);
-#pragma unroll
-    for (int col = 0; col < R; ++col)
-#pragma unroll
-      for (int r = 0; r < R; ++r) {
-        const double w = m[col * R + r];
-        v[r].x = fma(w, u[col].x, v[r].x);
-        v[r].y = fma(w, u[col].y, v[r].y);
-      }
-#pragma unroll
-    for (int i = 0; i < NF; ++i) {
-      dphi[i * n3 + e] = v[i];
-      dpi[i * n3 + e] = v[NF + i];
-    }
+  for (int i = 0; i < NF; ++i) {
+    dphi[i * stride + e] = v[i];
+    dpi[i * stride + e] = v[NF + i];
   }
 }
 
-__global__ void real_to_complex_kernel(const double* __restrict__ r, double2* __restrict__ c,
-                                       size_t n3, double shift) {
-  const size_t stride = size_t(gridDim.x) * blockDim.x;
-  for (size_t e = size_t(blockIdx.x) * blockDim.x + threadIdx.x; e < n3; e += stride)
-    c[e] = make_double2(r[e] - shift, 0.0);
+// Compensated sums of the 2 nf staged arrays (n^3 values each), kMeanBlocks
+// blocks per array, then their means.
+constexpr int kMeanBlocks = 128;
+__global__ __launch_bounds__(kBlock) void array_sums_kernel(const double* __restrict__ r, size_t n3,
+                                                           double* __restrict__ part) {
+  __shared__ KSum scratch[4];
+  const double* p = r + size_t(blockIdx.y) * n3;
+  KSum acc[1] = {{0.0, 0.0}};
+  const size_t stride = size_t(kMeanBlocks) * kBlock;
+#pragma unroll 4
+  for (size_t e = size_t(blockIdx.x) * kBlock + threadIdx.x; e < n3; e += stride) kadd(acc[0], p[e]);
+  block_reduce<1>(acc, scratch);
+  if (threadIdx.x == 0) {
+    double* o = part + 2 * (size_t(blockIdx.y) * kMeanBlocks + blockIdx.x);
+    o[0] = acc[0].s;
+    o[1] = acc[0].c;
+  }
 }
 
-__global__ void complex_to_real_kernel(const double2* __restrict__ c, double* __restrict__ r,
-                                       size_t n3, double scale, double add) {
-  const size_t stride = size_t(gridDim.x) * blockDim.x;
-  for (size_t e = size_t(blockIdx.x) * blockDim.x + threadIdx.x; e < n3; e += stride)
-    r[e] = fma(c[e].x, scale, add);
-}
-
-int grid_of(size_t work) {
-  const size_t b = (work + kBlock - 1) / kBlock;
-  return int(b < 65536 ? b : 65536);
+__global__ __launch_bounds__(64) void array_means_kernel(const double* __restrict__ part, double n3,
+                                                        double* __restrict__ mean) {
+  KSum t{0.0, 0.0};
+  for (int b = int(threadIdx.x); b < kMeanBlocks; b += 64) {
+    const double* p = part + 2 * (size_t(blockIdx.x) * kMeanBlocks + b);
+    t = kcombine(t, KSum{p[0], p[1]});
+  }
+  t = wave_reduce(t);
+  if (threadIdx.x == 0) mean[blockIdx.x] = (t.s + t.c) / n3;
 }
 
 // ---- dispatch over (potential family, fields) ------------------------------
@@ -396,7 +409,7 @@ struct LinFns {
   void (*table)(LinScalars*, LinConsts, PotArgs, Weights, double, int, double*);
   void (*growth[kGrowthVariants])(double*, const double*, long long, const double*, int, int);
   int cols[kGrowthVariants];
-  void (*apply)(double2*, double2*, const double*, int);
+  void (*apply)(double2*, double2*, const double*, FftPlan, size_t);
 };
 
 template <int KIND, int NF>
@@ -448,8 +461,10 @@ struct sl_linear {
   LinConsts K{};
   LinScalars host{};          // last background read back
   LinScalars* sc = nullptr;   // device background
-  double2* dphi = nullptr;    // nf * n^3 modes of the field perturbations
-  double2* dpi = nullptr;     // nf * n^3 modes of the momentum perturbations
+  FftPlan plan{};
+  size_t modes = 0;           // n^2 nhp values of a half spectrum (see fft.h)
+  double2* dphi = nullptr;    // nf half spectra of the field perturbations
+  double2* dpi = nullptr;     // nf half spectra of the momentum perturbations
   double* M = nullptr;        // ncls * (2 nf)^2 growth functions
   double* k2 = nullptr;       // ncls values of k_eff^2
   double* tab = nullptr;      // two buffers of kLinChunk stages of coefficients
@@ -457,10 +472,10 @@ struct sl_linear {
   hipEvent_t ev_tab[2] = {nullptr, nullptr};   // table chunk ready (per buffer)
   hipEvent_t ev_grow[2] = {nullptr, nullptr};  // growth chunk done with a buffer
   hipEvent_t ev_sync = nullptr;
-  double* stage = nullptr;    // n^3 doubles of host<->device staging
-  double2* fa = nullptr;      // transform scratch
-  double2* fb = nullptr;
-  double2* tw = nullptr;
+  double* stage = nullptr;    // 2 nf n^3 doubles: host fields, then momenta
+  double* means = nullptr;    // 2 nf means and their partial sums
+  double2* work = nullptr;    // one half spectrum of transform scratch
+  double2* tw = nullptr;      // twiddles and axis table of the transforms
   int growth_variant = -1;  // columns-per-lane variant, -1 until timed
   bool timing = false;
   // kind 0: one chunk (e0 -> e1 table on the aux stream, e2 -> e3 growth);
@@ -475,7 +490,7 @@ struct sl_linear {
 namespace {
 
 void lin_free(sl_linear* L) {
-  void* ptrs[] = {L->sc, L->dphi, L->dpi, L->M, L->k2, L->tab, L->stage, L->fa, L->fb, L->tw};
+  void* ptrs[] = {L->sc, L->dphi, L->dpi, L->M, L->k2, L->tab, L->stage, L->means, L->work, L->tw};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
   for (auto& r : L->recs)
@@ -515,14 +530,11 @@ sl_status lin_read(sl_linear* L) {
   return SL_OK;
 }
 
-// 3-D DFT fa -> fb (fa clobbered); sign -1 forward, +1 inverse (unnormalised).
-sl_status lin_dft3(sl_linear* L, int sign) {
-  const int n = L->cfg.n;
-  HIP_TRY(launch_twiddles(n, sign, L->tw, L->stream));
-  HIP_TRY(launch_dft_axis(n, L->fa, L->fb, L->tw, 0, L->stream));
-  HIP_TRY(launch_dft_axis(n, L->fb, L->fa, L->tw, 1, L->stream));
-  HIP_TRY(launch_dft_axis(n, L->fa, L->fb, L->tw, 2, L->stream));
-  return SL_OK;
+ModeBuf half_spectrum(const sl_linear* L, double2* p) {
+  ModeBuf B{};
+  B.seg[0][0] = p;
+  B.z1 = B.z2 = L->cfg.n;
+  return B;
 }
 
 sl_status lin_keff2(sl_linear* L) {
@@ -532,17 +544,6 @@ sl_status lin_keff2(sl_linear* L) {
   HIP_TRY(hipGetLastError());
   L->k2_valid = true;
   return SL_OK;
-}
-
-double compensated_mean(const double* v, size_t n) {
-  double s = 0.0, c = 0.0;
-  for (size_t i = 0; i < n; ++i) {
-    const double y = v[i] - c;
-    const double t = s + y;
-    c = (t - s) - y;
-    s = t;
-  }
-  return s / double(n);
 }
 
 }  // namespace
@@ -564,6 +565,8 @@ sl_status sl_linear_create(const sl_config* cfg, void* hip_stream, sl_linear** o
   const int n = cfg->n, nf = cfg->nfields;
   L->n3 = size_t(n) * n * n;
   L->ncls = class_count(n);
+  L->plan = fft_plan(n);
+  L->modes = size_t(n) * n * L->plan.nhp;
   if (hip_stream) {
     L->stream = static_cast<hipStream_t>(hip_stream);
   } else {
@@ -584,8 +587,8 @@ sl_status sl_linear_create(const sl_config* cfg, void* hip_stream, sl_linear** o
   L->K.expand = cfg->expansion == SL_EXPAND_SELF ? 1 : 0;
   const size_t R = 2 * size_t(nf);
   bool ok = hipMalloc(reinterpret_cast<void**>(&L->sc), sizeof(LinScalars)) == hipSuccess;
-  ok = ok && hipMalloc(reinterpret_cast<void**>(&L->dphi), nf * L->n3 * sizeof(double2)) == hipSuccess;
-  ok = ok && hipMalloc(reinterpret_cast<void**>(&L->dpi), nf * L->n3 * sizeof(double2)) == hipSuccess;
+  ok = ok && hipMalloc(reinterpret_cast<void**>(&L->dphi), nf * L->modes * sizeof(double2)) == hipSuccess;
+  ok = ok && hipMalloc(reinterpret_cast<void**>(&L->dpi), nf * L->modes * sizeof(double2)) == hipSuccess;
   ok = ok && hipMalloc(reinterpret_cast<void**>(&L->M), size_t(L->ncls) * R * R * sizeof(double)) == hipSuccess;
   ok = ok && hipMalloc(reinterpret_cast<void**>(&L->k2), size_t(L->ncls) * sizeof(double)) == hipSuccess;
   ok = ok && hipMalloc(reinterpret_cast<void**>(&L->tab),
@@ -596,10 +599,11 @@ sl_status sl_linear_create(const sl_config* cfg, void* hip_stream, sl_linear** o
     ok = ok && hipEventCreateWithFlags(&L->ev_grow[k], hipEventDisableTiming) == hipSuccess;
   }
   ok = ok && hipEventCreateWithFlags(&L->ev_sync, hipEventDisableTiming) == hipSuccess;
-  ok = ok && hipMalloc(reinterpret_cast<void**>(&L->stage), L->n3 * sizeof(double)) == hipSuccess;
-  ok = ok && hipMalloc(reinterpret_cast<void**>(&L->fa), L->n3 * sizeof(double2)) == hipSuccess;
-  ok = ok && hipMalloc(reinterpret_cast<void**>(&L->fb), L->n3 * sizeof(double2)) == hipSuccess;
-  ok = ok && hipMalloc(reinterpret_cast<void**>(&L->tw), size_t(n) * sizeof(double2)) == hipSuccess;
+  ok = ok && hipMalloc(reinterpret_cast<void**>(&L->stage), 2 * nf * L->n3 * sizeof(double)) == hipSuccess;
+  ok = ok && hipMalloc(reinterpret_cast<void**>(&L->means),
+                       2 * size_t(nf) * (1 + 2 * kMeanBlocks) * sizeof(double)) == hipSuccess;
+  ok = ok && hipMalloc(reinterpret_cast<void**>(&L->work), L->modes * sizeof(double2)) == hipSuccess;
+  ok = ok && hipMalloc(reinterpret_cast<void**>(&L->tw), size_t(n) * 3 * sizeof(double)) == hipSuccess;
   if (!ok) {
     lin_free(L);
     delete L;
@@ -609,9 +613,10 @@ sl_status sl_linear_create(const sl_config* cfg, void* hip_stream, sl_linear** o
   s.a = cfg->a0;
   L->host = s;
   (void)hipMemcpyAsync(L->sc, &s, sizeof s, hipMemcpyHostToDevice, L->stream);
-  (void)hipMemsetAsync(L->dphi, 0, nf * L->n3 * sizeof(double2), L->stream);
-  (void)hipMemsetAsync(L->dpi, 0, nf * L->n3 * sizeof(double2), L->stream);
-  if (hipStreamSynchronize(L->stream) != hipSuccess) {
+  (void)hipMemsetAsync(L->dphi, 0, nf * L->modes * sizeof(double2), L->stream);
+  (void)hipMemsetAsync(L->dpi, 0, nf * L->modes * sizeof(double2), L->stream);
+  if (launch_fft_tables(n, L->st, L->tw, reinterpret_cast<double*>(L->tw + n), L->stream) != hipSuccess ||
+      hipStreamSynchronize(L->stream) != hipSuccess) {
     lin_free(L);
     delete L;
     return fail(SL_E_DEVICE, "device initialisation failed");
@@ -687,29 +692,35 @@ sl_status sl_linear_set_fields(sl_linear* L, const double* phi, const double* pi
   s.a = L->cfg.a0;
   s.eta = 0.0;
   s.p_a = p_a;
+  // both arrays to the device and their means there (a compensated sum on the
+  // host was half of a call at 96^3); nothing of the state changes before
+  // they are known to be finite
+  const size_t count = size_t(nf) * L->n3;
+  HIP_TRY(hipMemcpyAsync(L->stage, phi, count * sizeof(double), hipMemcpyHostToDevice, L->stream));
+  HIP_TRY(hipMemcpyAsync(L->stage + count, pi, count * sizeof(double), hipMemcpyHostToDevice, L->stream));
+  double* part = L->means + 2 * nf;
+  hipLaunchKernelGGL(array_sums_kernel, dim3(kMeanBlocks, 2 * nf), dim3(kBlock), 0, L->stream, L->stage, L->n3,
+                     part);
+  HIP_TRY(hipGetLastError());
+  hipLaunchKernelGGL(array_means_kernel, dim3(2 * nf), dim3(64), 0, L->stream, part, double(L->n3), L->means);
+  HIP_TRY(hipGetLastError());
+  double mean[2 * kLinMaxFields];
+  HIP_TRY(hipMemcpyAsync(mean, L->means, 2 * nf * sizeof(double), hipMemcpyDeviceToHost, L->stream));
+  HIP_TRY(hipStreamSynchronize(L->stream));
   for (int i = 0; i < nf; ++i) {
-    s.phi0[i] = compensated_mean(phi + i * L->n3, L->n3);
-    s.pi0[i] = compensated_mean(pi + i * L->n3, L->n3);
+    s.phi0[i] = mean[i];
+    s.pi0[i] = mean[nf + i];
     if (!std::isfinite(s.phi0[i]) || !std::isfinite(s.pi0[i]))
       return fail(SL_E_INVALID, "fields must be finite");
   }
-  const unsigned gr = unsigned(grid_of(L->n3));
-  for (int arr = 0; arr < 2; ++arr) {
-    const double* src = arr == 0 ? phi : pi;
-    double2* dst = arr == 0 ? L->dphi : L->dpi;
-    for (int i = 0; i < nf; ++i) {
-      HIP_TRY(hipMemcpyAsync(L->stage, src + i * L->n3, L->n3 * sizeof(double), hipMemcpyHostToDevice,
-                             L->stream));
-      hipLaunchKernelGGL(real_to_complex_kernel, dim3(gr), dim3(kBlock), 0, L->stream, L->stage, L->fa,
-                         L->n3, arr == 0 ? s.phi0[i] : s.pi0[i]);
-      HIP_TRY(hipGetLastError());
-      sl_status st = lin_dft3(L, -1);
-      if (st != SL_OK) return st;
-      HIP_TRY(hipMemcpyAsync(dst + i * L->n3, L->fb, L->n3 * sizeof(double2), hipMemcpyDeviceToDevice,
-                             L->stream));
-      // the perturbation has zero lattice sum: its k = 0 mode is zero
-      HIP_TRY(hipMemsetAsync(dst + i * L->n3, 0, sizeof(double2), L->stream));
-    }
+  for (int k = 0; k < 2 * nf; ++k) {
+    double2* dst = k < nf ? L->dphi + k * L->modes : L->dpi + (k - nf) * L->modes;
+    const ModeBuf B = half_spectrum(L, dst);
+    HIP_TRY(launch_array_rows(L->stage + k * L->n3, L->means + k, L->plan, B, L->tw, L->stream));
+    HIP_TRY(launch_fft_columns(L->plan, B, B, L->tw, 1, 0, L->stream));
+    HIP_TRY(launch_fft_columns(L->plan, B, B, L->tw, 2, 0, L->stream));
+    // the perturbation has zero lattice sum: its k = 0 mode is zero
+    HIP_TRY(hipMemsetAsync(dst, 0, sizeof(double2), L->stream));
   }
   HIP_TRY(hipMemcpyAsync(L->sc, &s, sizeof s, hipMemcpyHostToDevice, L->stream));
   if (std::isnan(p_a)) {
@@ -846,8 +857,8 @@ sl_status sl_linear_evolve(sl_linear* L, int64_t steps, double dt, int32_t order
     a1 = L->recs[r].e[1];
     HIP_TRY(hipEventRecord(a0, L->stream));
   }
-  hipLaunchKernelGGL(f.apply, dim3(unsigned(grid_of(L->n3))), dim3(kBlock), 0, L->stream, L->dphi,
-                     L->dpi, L->M, L->cfg.n);
+  hipLaunchKernelGGL(f.apply, dim3(unsigned((L->cfg.n * L->plan.nhp + kBlock - 1) / kBlock), unsigned(L->cfg.n)),
+                     dim3(kBlock), 0, L->stream, L->dphi, L->dpi, L->M, L->plan, L->modes);
   HIP_TRY(hipGetLastError());
   if (L->timing) HIP_TRY(hipEventRecord(a1, L->stream));
   return SL_OK;
@@ -859,23 +870,22 @@ sl_status sl_linear_get_fields(sl_linear* L, double* phi_out, double* pi_out) {
   sl_status st = lin_read(L);
   if (st != SL_OK) return st;
   const int nf = L->cfg.nfields;
-  const unsigned gr = unsigned(grid_of(L->n3));
   const double inv = 1.0 / double(L->n3);
+  const size_t count = size_t(nf) * L->n3;
+  const ModeBuf W = half_spectrum(L, L->work);
   for (int arr = 0; arr < 2; ++arr) {
     double* out = arr == 0 ? phi_out : pi_out;
     if (!out) continue;
-    const double2* src = arr == 0 ? L->dphi : L->dpi;
+    const double* zero = arr == 0 ? L->sc->phi0 : L->sc->pi0;  // device addresses
     for (int i = 0; i < nf; ++i) {
-      HIP_TRY(hipMemcpyAsync(L->fa, src + i * L->n3, L->n3 * sizeof(double2), hipMemcpyDeviceToDevice,
-                             L->stream));
-      st = lin_dft3(L, +1);
-      if (st != SL_OK) return st;
-      hipLaunchKernelGGL(complex_to_real_kernel, dim3(gr), dim3(kBlock), 0, L->stream, L->fb, L->stage,
-                         L->n3, inv, arr == 0 ? L->host.phi0[i] : L->host.pi0[i]);
-      HIP_TRY(hipGetLastError());
-      HIP_TRY(hipMemcpyAsync(out + i * L->n3, L->stage, L->n3 * sizeof(double), hipMemcpyDeviceToHost,
-                             L->stream));
+      const ModeBuf B = half_spectrum(L, (arr == 0 ? L->dphi : L->dpi) + i * L->modes);
+      HIP_TRY(launch_fft_columns(L->plan, B, W, L->tw, 2, 1, L->stream));
+      HIP_TRY(launch_fft_columns(L->plan, W, W, L->tw, 1, 1, L->stream));
+      HIP_TRY(launch_rows_to_array(L->stage + arr * count + i * L->n3, inv, zero + i, L->plan, W, L->tw,
+                                   L->stream));
     }
+    HIP_TRY(hipMemcpyAsync(out, L->stage + arr * count, count * sizeof(double), hipMemcpyDeviceToHost,
+                           L->stream));
   }
   HIP_TRY(hipStreamSynchronize(L->stream));
   return SL_OK;

@@ -427,39 +427,6 @@ void free_all(sl_lattice* L) {
   if (L->own_stream && L->stream) (void)hipStreamDestroy(L->stream);
 }
 
-// Complex scratch for the transforms: two n^3 arrays and a twiddle table.
-struct FftScratch {
-  double2* a = nullptr;
-  double2* b = nullptr;
-  double2* tw = nullptr;
-  ~FftScratch() {
-    if (a) (void)hipFree(a);
-    if (b) (void)hipFree(b);
-    if (tw) (void)hipFree(tw);
-  }
-};
-
-sl_status fft_alloc(sl_lattice* L, FftScratch& S) {
-  const size_t bytes = L->n3 * sizeof(double2);
-  if (hipMalloc(&S.a, bytes) != hipSuccess || hipMalloc(&S.b, bytes) != hipSuccess ||
-      hipMalloc(&S.tw, size_t(L->cfg.n) * sizeof(double2)) != hipSuccess)
-    return fail(SL_E_NOMEM, "cannot allocate transform scratch (%zu bytes)", 2 * bytes);
-  return SL_OK;
-}
-
-// 3-D DFT a -> b (a is clobbered); sign +1: sum f_n exp(+2 pi i n.j/N).
-// 3-D DFT of a into b (a is overwritten); tw holds n twiddles.
-sl_status dft3(sl_lattice* L, double2* a, double2* b, double2* tw, int sign) {
-  const int n = L->cfg.n;
-  HIP_TRY(launch_twiddles(n, sign, tw, L->stream));
-  HIP_TRY(launch_dft_axis(n, a, b, tw, 0, L->stream));
-  HIP_TRY(launch_dft_axis(n, b, a, tw, 1, L->stream));
-  HIP_TRY(launch_dft_axis(n, a, b, tw, 2, L->stream));
-  return SL_OK;
-}
-
-sl_status dft3(sl_lattice* L, FftScratch& S, int sign) { return dft3(L, S.a, S.b, S.tw, sign); }
-
 // Largest scratch a spectrum call may take from the static array: two complex
 // n^3 arrays, twiddles and 3 nbins binning sums of up to 256 workgroups.
 size_t spectrum_noalloc_bytes(int n, int nbins) {
@@ -570,7 +537,7 @@ sl_status spectrum_check(sl_lattice* L, int field, int nbins, const double* k_ou
 // x and y passes of a field's (or its momenta's) transform into the scratch.
 hipError_t transform_rows(sl_lattice* L, int field, int momentum, const SpecScratch& S) {
   hipError_t e = launch_field_rows(L->v, field, momentum, S.P, S.B, S.tw, L->stream);
-  if (e == hipSuccess) e = launch_fft_columns(S.P, S.B, S.tw, 1, 0, L->stream);
+  if (e == hipSuccess) e = launch_fft_columns(S.P, S.B, S.B, S.tw, 1, 0, L->stream);
   return e;
 }
 
@@ -933,32 +900,40 @@ sl_status sl_init_fluctuations(sl_lattice* L, const double* phi0, const double* 
     }
   }
   HIP_TRY(launch_reset_scalars(L->v, L->cfg.a0, 0.0, off, L->stream));
-  HIP_TRY(launch_fill_homogeneous(L->v, phi0, pi0, off, L->stream));
   if (kind == SL_FLUCT_VACUUM) {
-    FftScratch S;
-    sl_status st = fft_alloc(L, S);
+    // z, y and x passes of the inverse transform, the last one into buffer 0
+    // (the scratch is buffer 1: the parity has just been reset)
+    SpecScratch S;
+    sl_status st = spec_scratch(L, 1, 1, nullptr, 0, S);
     if (st != SL_OK) return st;
+    HIP_TRY(launch_fft_tables(L->cfg.n, L->v.st, S.tw, S.ax, L->stream));
     for (int i = 0; i < nf; ++i) {
-      HIP_TRY(launch_vacuum_modes(L->v, S.a, i, m2eff[i], amplitude, seed, L->stream));
-      st = dft3(L, S, +1);
-      if (st != SL_OK) return st;
-      HIP_TRY(launch_add_real(L->v, S.b, i, base[i], 1.0, L->stream));
+      HIP_TRY(launch_vacuum_columns(L->v, i, m2eff[i], amplitude, seed, S.P, S.B, S.tw, S.ax, L->stream));
+      HIP_TRY(launch_fft_columns(S.P, S.B, S.B, S.tw, 1, 1, L->stream));
+      HIP_TRY(launch_rows_to_field(L->v, i, base[i], pi0[i] - off.pi[i], S.P, S.B, S.tw, L->stream));
     }
-    HIP_TRY(hipStreamSynchronize(L->stream));
-  } else if (kind == SL_FLUCT_WHITE) {
-    double* g = nullptr;
-    double* mean = nullptr;
-    if (hipMalloc(&g, L->n3 * sizeof(double)) != hipSuccess ||
-        hipMalloc(&mean, sizeof(double)) != hipSuccess) {
-      if (g) (void)hipFree(g);
-      return fail(SL_E_NOMEM, "cannot allocate white-noise scratch");
+    if (S.owned) HIP_TRY(hipStreamSynchronize(L->stream));
+  } else {
+    HIP_TRY(launch_fill_homogeneous(L->v, phi0, pi0, off, L->stream));
+  }
+  if (kind == SL_FLUCT_WHITE) {
+    // the normals of one field: in buffer 1 where its first array (the block,
+    // when phi and pi are interleaved by plane) holds n^3 doubles
+    const bool block = L->v.zs == 2 * nf;
+    double* g = static_cast<double*>(L->v.phi[1]);
+    double* owned = nullptr;
+    if (L->n3 * nf * L->elem * (block ? 2 : 1) < L->n3 * sizeof(double)) {
+      if (hipMalloc(&owned, L->n3 * sizeof(double)) != hipSuccess)
+        return fail(SL_E_NOMEM, "cannot allocate white-noise scratch");
+      g = owned;
     }
     hipError_t e = hipSuccess;
     for (int i = 0; i < nf && e == hipSuccess; ++i)
-      e = launch_white(L->v, g, mean, i, base[i], amplitude, seed, L->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(L->stream);
-    (void)hipFree(g);
-    (void)hipFree(mean);
+      e = launch_white(L->v, g, L->sums_dev, i, base[i], amplitude, seed, L->stream);
+    if (owned) {
+      if (e == hipSuccess) e = hipStreamSynchronize(L->stream);
+      (void)hipFree(owned);
+    }
     if (e != hipSuccess) return fail(SL_E_DEVICE, "white-noise initialisation: %s", hipGetErrorString(e));
   }
   HIP_TRY(launch_energies(L->v, L->sums_dev, L->energies_dev, 1, L->stream));
