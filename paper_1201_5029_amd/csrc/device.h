@@ -44,17 +44,94 @@ __device__ __forceinline__ KSum kcombine(KSum a, KSum b) {
   return r;
 }
 
-// Butterfly over the 64 lanes of a wavefront (fixed xor pattern).
-__device__ __forceinline__ KSum wave_reduce(KSum v) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) {
-    KSum o;
-    o.s = __shfl_xor(v.s, off, 64);
-    o.c = __shfl_xor(v.c, off, 64);
-    v = kcombine(v, o);
-  }
-  return v;
+// Sum over the 64 lanes of a wavefront, in all lanes: a butterfly in a fixed
+// order.  Within a row of 16 lanes the partners are DPP permutations (lane ^ 1,
+// lane ^ 2, and, with the quads and then the halves uniform, the mirror images
+// of the half row and of the row); the rows meet through the lane swaps, which
+// leave both partners' values in every lane.  (A step through LDS, as
+// __shfl_xor takes, costs about twice as much; the reductions at both ends of
+// a pass bound the smallest lattices.)
+template <int CTRL>
+__device__ __forceinline__ double dpp_move(double x) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), CTRL, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), CTRL, 0xf, 0xf, true);
+  return __hiloint2double(hi, lo);
 }
+
+template <int CTRL>
+__device__ __forceinline__ KSum dpp_combine(KSum v) {
+  return kcombine(v, KSum{dpp_move<CTRL>(v.s), dpp_move<CTRL>(v.c)});
+}
+
+// Exchange the odd rows of a (HALF: its upper half) with the even rows (lower
+// half) of b: x = a's even and b's even rows, y = a's odd and b's odd rows, so
+// that x + y sums a over each pair of rows in the even rows and b in the odd
+// ones (a = b: a in both).
+template <bool HALF>
+__device__ __forceinline__ double2 lane_swap(double a, double b) {
+  const unsigned al = unsigned(__double2loint(a)), ah = unsigned(__double2hiint(a));
+  const unsigned bl = unsigned(__double2loint(b)), bh = unsigned(__double2hiint(b));
+  const auto l = HALF ? __builtin_amdgcn_permlane32_swap(al, bl, false, false)
+                      : __builtin_amdgcn_permlane16_swap(al, bl, false, false);
+  const auto h = HALF ? __builtin_amdgcn_permlane32_swap(ah, bh, false, false)
+                      : __builtin_amdgcn_permlane16_swap(ah, bh, false, false);
+  return make_double2(__hiloint2double(int(h[0]), int(l[0])), __hiloint2double(int(h[1]), int(l[1])));
+}
+
+template <bool HALF>
+__device__ __forceinline__ KSum swap_combine(KSum a, KSum b) {
+  const double2 s = lane_swap<HALF>(a.s, b.s), c = lane_swap<HALF>(a.c, b.c);
+  return kcombine(KSum{s.x, c.x}, KSum{s.y, c.y});
+}
+
+__device__ __forceinline__ KSum wave_reduce(KSum v) {
+  v = dpp_combine<0xB1>(v);   // quad_perm [1, 0, 3, 2]
+  v = dpp_combine<0x4E>(v);   // quad_perm [2, 3, 0, 1]
+  v = dpp_combine<0x141>(v);  // row_half_mirror
+  v = dpp_combine<0x140>(v);  // row_mirror
+  v = swap_combine<false>(v, v);
+  return swap_combine<true>(v, v);
+}
+
+// Three sums over a wavefront at once: the first exchanges leave the halves,
+// then the rows, with different quantities, so that 7 combinations do the work
+// of 18.  Every lane of row 0 gets the first, of row 2 the second, of row 1
+// the third total (row 3: zero).
+__device__ __forceinline__ KSum wave_reduce3(const KSum (&v)[3]) {
+  const KSum a = swap_combine<true>(v[0], v[1]);
+  const KSum b = swap_combine<true>(v[2], KSum{0.0, 0.0});
+  KSum t = swap_combine<false>(a, b);
+  t = dpp_combine<0xB1>(t);
+  t = dpp_combine<0x4E>(t);
+  t = dpp_combine<0x141>(t);
+  return dpp_combine<0x140>(t);
+}
+
+// Three sums over a 256-thread workgroup (scratch: 12 KSum of LDS): the totals
+// of quantity q are in lanes 4 q .. 4 q + 3 of each row of 16 lanes, q < 3.
+// Contains one barrier: all threads call, and scratch may be written again
+// after the next barrier.
+__device__ __forceinline__ KSum block_reduce3(const KSum (&v)[3], KSum* scratch) {
+  static_assert(kBlock == 256, "four wavefronts");
+  const int lane = int(threadIdx.x) & 63, wave = int(threadIdx.x) >> 6;
+  const KSum t = wave_reduce3(v);
+  const int row = lane >> 4, q = row == 0 ? 0 : (row == 2 ? 1 : 2);
+  if ((lane & 15) == 0 && row < 3) scratch[4 * q + wave] = t;
+  __syncthreads();
+  const int l = lane & 15;
+  KSum w = scratch[l < 12 ? l : 0];
+  w = dpp_combine<0xB1>(w);
+  return dpp_combine<0x4E>(w);
+}
+
+// A lane's value in every lane (scalar registers).
+__device__ __forceinline__ double read_lane(double x, int lane) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), lane),
+                          __builtin_amdgcn_readlane(__double2loint(x), lane));
+}
+
+// b / d for b d < 2^32 with m = magic_of(d).
+__device__ __forceinline__ int div_magic(int b, unsigned m) { return m ? int(__umulhi(unsigned(b), m)) : b; }
 
 // Offset of site e = (z n + y) n + x of field i in a field array whose
 // planes are zs n^2 elements apart (the fields of a plane one after the

@@ -137,9 +137,6 @@ __device__ __forceinline__ void dft_r(double2 (&v)[8]) {
   }
 }
 
-// b / d for b d < 2^32 with m = ceil(2^32 / d) (0 stands for d = 1).
-__device__ __forceinline__ int div_magic(int b, unsigned m) { return m ? int(__umulhi(unsigned(b), m)) : b; }
-
 // How the values of a group of lines sit in LDS and how threads share them.
 // Rows (the x axis, contiguous in memory): neighbouring threads take
 // neighbouring elements of a line.

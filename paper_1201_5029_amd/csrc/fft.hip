@@ -209,10 +209,6 @@ __global__ __launch_bounds__(NT, NT == 256 ? 3 : 4) void fft_columns_kernel(FftP
 
 // ---- host side --------------------------------------------------------------
 
-namespace {
-unsigned magic_of(int d) { return d <= 1 ? 0u : unsigned(((1ull << 32) + d - 1) / d); }
-}  // namespace
-
 FftPlan fft_plan(int n) {
   FftPlan P{};
   P.n = n;

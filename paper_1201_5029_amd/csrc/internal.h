@@ -114,6 +114,9 @@ struct Stencil {
   int32_t pad;
 };
 
+// Constant of a division by d (see div_magic): ceil(2^32 / d), 0 for d = 1.
+inline unsigned magic_of(int d) { return d <= 1 ? 0u : unsigned(((1ull << 32) + d - 1) / d); }
+
 // Launch shape of the tiled passes: TX lanes in x (8 .. 64) each holding VX
 // consecutive sites (tile width TX*VX), TY = floor(256/TX) rows in y (the
 // last 256 - TX*TY lanes of the workgroup idle), TZ planes per z-chunk.
@@ -155,6 +158,7 @@ struct PassParams {
   int n;
   int tx, ty, tz;  // lanes in x, rows, planes per chunk
   int ntx, nty, ntz;
+  unsigned m_tx, m_ntx, m_nty;  // division constants of tx, ntx, nty
   int zs;  // plane stride of the field arrays, in planes (LatView::zs)
 };
 

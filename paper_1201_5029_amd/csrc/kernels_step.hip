@@ -32,6 +32,8 @@
 // y so the four in-plane neighbours come from LDS.  Halo cells are loaded
 // and drifted by designated threads.
 
+#include <cstddef>
+
 #include "device.h"
 
 namespace symlat {
@@ -127,16 +129,42 @@ __device__ __forceinline__ int xcd_tile(int b, int nb) {
   return x * per + (x < rem ? x : rem) + i;
 }
 
+// Column, row and chunk of a tile (x tiles fastest, then y, then z chunks);
+// the divisions are multiplications by constants the host prepares, since
+// every workgroup waits for them before its first load.
+__device__ __forceinline__ void tile_of(const PassParams& P, int tile, int& xt, int& yt, int& zt) {
+  const int row = div_magic(tile, P.m_ntx);
+  xt = tile - row * P.ntx;
+  zt = div_magic(row, P.m_nty);
+  yt = row - zt * P.nty;
+}
+
+// What a pass needs of the stage scalars, in every thread's registers.
+template <int NF>
+struct StageIn {
+  double c, alpha, beta;
+  double off_phi[NF], off_pi[NF];
+};
+
+// A tile's three sums, as (sum, compensation) pairs, into its record.
+__device__ __forceinline__ void store_partials(const PassParams& P, const Chain& C, int tile,
+                                               const KSum (&v)[3], KSum* scratch) {
+  const KSum t = block_reduce3(v, scratch);
+  const int id = int(threadIdx.x);
+  if (id < 12 && (id & 3) == 0)
+    *reinterpret_cast<double2*>(P.partials[C.p_out] + size_t(tile) * 6 + (id >> 1)) = make_double2(t.s, t.c);
+}
+
 // FP32 storage: the offsets of the state this pass writes -- the homogeneous
 // parts of the stage's drift and kick, fbar = off_phi + c off_pi and
 // pibar = off_pi - beta dV(fbar), in FP64 (every lane forms the same values)
 // -- and the constants of the difference form of dV around fbar.  The first
 // tile records them for the stage update (finalize or next chained pass).
 template <int KIND, int NF, typename T>
-__device__ __forceinline__ void split_offsets(const PassParams& P, const DevScalars& S,
+__device__ __forceinline__ void split_offsets(const PassParams& P, const StageIn<NF>& S,
                                               double* offs_out, int tile_id, double (&fbar)[NF],
                                               double (&pibar)[NF], T (&fbT)[NF], SplitK<T>& sk) {
-  const double c = S.c_next, beta = S.beta;
+  const double c = S.c, beta = S.beta;
   PotT<double> pd;
 #pragma unroll
   for (int k = 0; k < kMaxFields; ++k) pd.p[k] = P.prm.p[k];
@@ -159,9 +187,10 @@ __device__ __forceinline__ void split_offsets(const PassParams& P, const DevScal
   }
 }
 
-// The scalars of this stage into S (LDS, every thread of the workgroup sees
-// them after the barrier): read from buffer s_in, or, for a chained pass,
-// formed by finishing the previous stage (see Chain).  All threads call.
+// The scalars of this stage in every thread: read from buffer s_in (through S
+// in LDS, which keeps them for the next tile of the same run), or, for a
+// chained pass, formed by finishing the previous stage (see Chain).  All
+// threads call.
 // A chained pass reads the previous stage's records (scalar words, offset
 // record, this thread's share of the per-tile partials) at the very start,
 // before the loads that depend on the state's parity, so that they are
@@ -172,9 +201,9 @@ struct ChainPre {
   double p[4][6];
 };
 __device__ void chain_prefetch(const PassParams& P, const Chain& C, ChainPre& cp);
-template <bool CH>
-__device__ void stage_scalars(const PassParams& P, const Chain& C, int tile_id, DevScalars& S,
-                              KSum* scratch, bool fresh, const ChainPre& cp);
+template <bool CH, int NF>
+__device__ __forceinline__ void stage_scalars(const PassParams& P, const Chain& C, int tile_id, DevScalars& S,
+                                              KSum* scratch, bool fresh, const ChainPre& cp, StageIn<NF>& in);
 
 // PF = 1: the next plane is loaded at the top of each z-iteration and used
 // at once.  PF = 2: software pipeline -- the loads for plane z+1 (own column
@@ -220,19 +249,15 @@ __device__ __forceinline__ void pass_tile(const PassParams& P, const Chain& C, i
   const int n = P.n;
   const size_t n2 = size_t(n) * n;
 
-  // tile of this workgroup (x tiles fastest, then y, then z chunks)
-  int b = tile_id;
-  const int xt = b % P.ntx;
-  b /= P.ntx;
-  const int yt = b % P.nty;
-  const int zt = b / P.nty;
+  int xt, yt, zt;
+  tile_of(P, tile_id, xt, yt, zt);
   const int TW = P.tx * VX;  // tile width in sites
   const int x0 = xt * TW, y0 = yt * P.ty, z0 = zt * P.tz;
   const int wx = min(TW, n - x0), wy = min(P.ty, n - y0), zc = min(P.tz, n - z0);
   const int zend = z0 + zc;  // exclusive; plane zend (mod n) is the upper halo
 
   const int tid = threadIdx.x;
-  const int ty = tid / P.tx;  // lanes past TX*TY (ty = TY) are idle
+  const int ty = div_magic(tid, P.m_tx);  // lanes past TX*TY (ty = TY) are idle
   const int tx = tid - ty * P.tx;
   const bool active = (tx * VX < wx) && (ty < wy);
   const int LX = TW + 2;
@@ -253,18 +278,18 @@ __device__ __forceinline__ void pass_tile(const PassParams& P, const Chain& C, i
     const int TX = P.tx, TY = P.ty;
     int hx = -1, hy = 0;
     if (tid < TX) {
-      if (tid * VX < wx) { hjob = 1; hx = x0 + tid * VX; hy = (y0 - 1 + n) % n; hl = 1 + tid * VX; }
+      if (tid * VX < wx) { hjob = 1; hx = x0 + tid * VX; hy = y0 == 0 ? n - 1 : y0 - 1; hl = 1 + tid * VX; }
     } else if (tid < 2 * TX) {
       const int t = tid - TX;
-      if (t * VX < wx) { hjob = 1; hx = x0 + t * VX; hy = (y0 + wy) % n; hl = (wy + 1) * LX + 1 + t * VX; }
+      if (t * VX < wx) { hjob = 1; hx = x0 + t * VX; hy = y0 + wy == n ? 0 : y0 + wy; hl = (wy + 1) * LX + 1 + t * VX; }
     } else if (tid < 2 * TX + TY) {
       const int r = tid - 2 * TX;
       // group [x0 - VX, x0) holds the left neighbour x0 - 1 as element VX - 1
-      if (r < wy) { hjob = 2; hx = (x0 - VX + n) % n; hy = y0 + r; hl = (r + 1) * LX; }
+      if (r < wy) { hjob = 2; hx = x0 == 0 ? n - VX : x0 - VX; hy = y0 + r; hl = (r + 1) * LX; }
     } else if (tid < 2 * TX + 2 * TY) {
       const int r = tid - 2 * TX - TY;
       // group [x0 + wx, x0 + wx + VX) holds the right neighbour as element 0
-      if (r < wy) { hjob = 3; hx = (x0 + wx) % n; hy = y0 + r; hl = (r + 1) * LX + wx + 1; }
+      if (r < wy) { hjob = 3; hx = x0 + wx == n ? 0 : x0 + wx; hy = y0 + r; hl = (r + 1) * LX + wx + 1; }
     }
     if (hx >= 0) hcol = size_t(hy) * n + hx;
   }
@@ -338,7 +363,7 @@ __device__ __forceinline__ void pass_tile(const PassParams& P, const Chain& C, i
   T mph[NF][VX], mpi[NF][VX], cph[NF][VX], cpi[NF][VX];
   // second register set of the depth-3 pipeline (the first: nph/npi, hph/hpi)
   [[maybe_unused]] T qph[NF][VX], qpi[NF][VX], gph[NF][VX], gpi[NF][VX];
-  load_own_into((z0 - 1 + n) % n, mph, mpi);
+  load_own_into(z0 == 0 ? n - 1 : z0 - 1, mph, mpi);
   load_own_into(z0, cph, cpi);
   if constexpr (PF == 2) {
     load_own(wrap(z0 + 1));
@@ -361,11 +386,12 @@ __device__ __forceinline__ void pass_tile(const PassParams& P, const Chain& C, i
 #pragma unroll
     for (int i = 0; i < 2 * NF; ++i) stv<T, VX>(sink + i * VX, zero);
   }
-  stage_scalars<CH>(P, C, tile_id, S, red_scratch, fresh, cp);
-  c = static_cast<T>(S.c_next);
-  alpha = static_cast<T>(S.alpha);
-  beta = static_cast<T>(S.beta);
-  if constexpr (kSplit) split_offsets<KIND, NF, T>(P, S, P.offs[C.p_out], tile_id, fbar, pibar, fbT, sk);
+  StageIn<NF> in;
+  stage_scalars<CH, NF>(P, C, tile_id, S, red_scratch, fresh, cp, in);
+  c = static_cast<T>(in.c);
+  alpha = static_cast<T>(in.alpha);
+  beta = static_cast<T>(in.beta);
+  if constexpr (kSplit) split_offsets<KIND, NF, T>(P, in, P.offs[C.p_out], tile_id, fbar, pibar, fbT, sk);
 #pragma unroll
   for (int i = 0; i < NF; ++i)
 #pragma unroll
@@ -512,13 +538,7 @@ __device__ __forceinline__ void pass_tile(const PassParams& P, const Chain& C, i
   }
 
   KSum v3[3] = {acc_dd, acc_v, acc_p};
-  block_reduce<3>(v3, red_scratch);
-  if (threadIdx.x == 0) {
-    double* out = P.partials[C.p_out] + size_t(tile_id) * 6;
-    out[0] = v3[0].s; out[1] = v3[0].c;
-    out[2] = v3[1].s; out[3] = v3[1].c;
-    out[4] = v3[2].s; out[5] = v3[2].c;
-  }
+  store_partials(P, C, tile_id, v3, red_scratch);
 }
 
 // The same stage pass with any member of the cubic stencil family of
@@ -563,18 +583,15 @@ __device__ __forceinline__ void pass_tile27(const PassParams& P, const Chain& C,
   const int n = P.n;
   const size_t n2 = size_t(n) * n;
 
-  int b = tile_id;
-  const int xt = b % P.ntx;
-  b /= P.ntx;
-  const int yt = b % P.nty;
-  const int zt = b / P.nty;
+  int xt, yt, zt;
+  tile_of(P, tile_id, xt, yt, zt);
   const int TW = P.tx * VX;
   const int x0 = xt * TW, y0 = yt * P.ty, z0 = zt * P.tz;
   const int wx = min(TW, n - x0), wy = min(P.ty, n - y0), zc = min(P.tz, n - z0);
   const int zend = z0 + zc;
 
   const int tid = threadIdx.x;
-  const int ty = tid / P.tx;  // lanes past TX*TY (ty = TY) are idle
+  const int ty = div_magic(tid, P.m_tx);  // lanes past TX*TY (ty = TY) are idle
   const int tx = tid - ty * P.tx;
   const bool active = (tx * VX < wx) && (ty < wy);
   const int LX = TW + 2;
@@ -590,8 +607,8 @@ __device__ __forceinline__ void pass_tile27(const PassParams& P, const Chain& C,
   {
     const int TX = P.tx, TY = P.ty;
     int hx = -1, hy = 0;
-    const int gl = (x0 - VX + n) % n, gr = (x0 + wx) % n;  // aligned groups
-    const int yb = (y0 - 1 + n) % n, ya = (y0 + wy) % n;
+    const int gl = x0 == 0 ? n - VX : x0 - VX, gr = x0 + wx == n ? 0 : x0 + wx;  // aligned groups
+    const int yb = y0 == 0 ? n - 1 : y0 - 1, ya = y0 + wy == n ? 0 : y0 + wy;
     if (tid < TX) {
       if (tid * VX < wx) { hjob = 1; hx = x0 + tid * VX; hy = yb; hl = 1 + tid * VX; }
     } else if (tid < 2 * TX) {
@@ -644,11 +661,12 @@ __device__ __forceinline__ void pass_tile27(const PassParams& P, const Chain& C,
   T* sink = static_cast<T*>(P.sink) + size_t(tid) * (2 * NF * VX);
   load_plane(wrapz(z0 - 1));
   // the stage scalars are formed while the first plane is in flight
-  stage_scalars<CH>(P, C, tile_id, S, red_scratch, fresh, cp);
-  c = static_cast<T>(S.c_next);
-  alpha = static_cast<T>(S.alpha);
-  beta = static_cast<T>(S.beta);
-  if constexpr (kSplit) split_offsets<KIND, NF, T>(P, S, P.offs[C.p_out], tile_id, fbar, pibar, fbT, sk);
+  StageIn<NF> in;
+  stage_scalars<CH, NF>(P, C, tile_id, S, red_scratch, fresh, cp, in);
+  c = static_cast<T>(in.c);
+  alpha = static_cast<T>(in.alpha);
+  beta = static_cast<T>(in.beta);
+  if constexpr (kSplit) split_offsets<KIND, NF, T>(P, in, P.offs[C.p_out], tile_id, fbar, pibar, fbT, sk);
   // same trailing sequence as an iteration (loads, then 2 NF stores) so the
   // wait at the loop head covers the loads only
 #pragma unroll
@@ -751,13 +769,7 @@ __device__ __forceinline__ void pass_tile27(const PassParams& P, const Chain& C,
   }
 
   KSum v3[3] = {acc_dd, acc_v, acc_p};
-  block_reduce<3>(v3, red_scratch);
-  if (threadIdx.x == 0) {
-    double* o = P.partials[C.p_out] + size_t(tile_id) * 6;
-    o[0] = v3[0].s; o[1] = v3[0].c;
-    o[2] = v3[1].s; o[3] = v3[1].c;
-    o[4] = v3[2].s; o[5] = v3[2].c;
-  }
+  store_partials(P, C, tile_id, v3, red_scratch);
 }
 
 // ST: 0 = 7-point pass, 1 = any member of the cubic family (27-point pass),
@@ -884,47 +896,90 @@ typedef double __attribute__((may_alias)) word_t;
 constexpr int kScalarWords = int(sizeof(DevScalars) / sizeof(double));
 static_assert(sizeof(DevScalars) % sizeof(double) == 0 && kScalarWords <= 64,
               "scalar record read as 8-byte words by the first wavefront");
+constexpr int kWordHist = int(offsetof(DevScalars, hist) / sizeof(double));
+constexpr int kWordOffs = int(offsetof(DevScalars, off_phi) / sizeof(double));
+static_assert(offsetof(DevScalars, hist_cap) / sizeof(double) == kWordHist + 1 &&
+                  offsetof(DevScalars, off_pi) / sizeof(double) == kWordOffs + kMaxFields &&
+                  kScalarWords == kWordOffs + 2 * kMaxFields,
+              "words stored by their threads");
 
-// Second half of a stage update: publish this thread's scalar/offset word
-// in LDS, reduce the partial sums over the workgroup, and let thread 0
-// finish the stage.
-__device__ void stage_update_finish(double word, KSum (&v)[3], const BgConsts& K, double w,
-                                    double w_next, double h, int has_next, int end_of_step,
-                                    bool record, KSum* scratch, DevScalars& S_io) {
+// Second half of a stage update: publish this thread's scalar/offset word in
+// LDS, reduce the partial sums over the workgroup and finish the stage.  Every
+// thread forms the same new scalars after the one barrier: a pass that chains
+// needs them in all of them.  `out`, if not NULL (one workgroup), receives the
+// new record: thread 0 stores what the update changes, the threads that hold
+// the other words store those, so that nobody waits for the whole record.
+// The smallest lattices are bound by this chain of dependent instructions and
+// the reduction at the end of the pass: with both going through shuffles in
+// LDS and one thread's update behind a second barrier a 32^3 FP64 stage took
+// 7.3 us, now 4.8.
+__device__ __forceinline__ void stage_update_finish(double word, const KSum (&v)[3], const BgConsts& K,
+                                                    double w, double w_next, double h, int has_next,
+                                                    int end_of_step, KSum* scratch, DevScalars& S_io,
+                                                    DevScalars* out, DevScalars& S) {
   __shared__ double offs_sh[2 * kMaxFields];
   const int t = threadIdx.x;
   if (t < kScalarWords)
     reinterpret_cast<word_t*>(&S_io)[t] = word;
   else if (t >= 64 && t < 64 + 2 * kMaxFields)
     offs_sh[t - 64] = word;
-  block_reduce<3>(v, scratch);  // its barriers publish the two LDS copies
+  const KSum tot = block_reduce3(v, scratch);  // its barrier publishes the two records
+  const double sum = tot.s + tot.c;
+  const double SdD = read_lane(sum, 0), SV = read_lane(sum, 4), S2 = read_lane(sum, 8);
+  S.p_a = S_io.p_a;
+  S.a_kick = S_io.a_kick;
+  S.a = S_io.a;
+#pragma unroll
+  for (int i = 0; i < kMaxFields; ++i) {
+    S.off_phi[i] = S_io.off_phi[i];
+    S.off_pi[i] = S_io.off_pi[i];
+  }
+  end_stage(S, K, offs_sh, w, h, SdD, SV, S2);
+  const double pa_end = S.p_a, a_end = S.a;
+  if (has_next) {
+    begin_stage(S, K, w_next, h);
+  } else {
+    S.c_next = S_io.c_next;
+    S.alpha = S_io.alpha;
+    S.beta = S_io.beta;
+  }
+  if (out == nullptr) return;
   if (t == 0) {
-    DevScalars S = S_io;
-    const double SdD = v[0].s + v[0].c;
-    const double SV = v[1].s + v[1].c;
-    const double S2 = v[2].s + v[2].c;
-    end_stage(S, K, offs_sh, w, h, SdD, SV, S2);
-    S.parity ^= 1;
-    if (end_of_step) S.eta = S.eta + h;
-    if (end_of_step && S.hist != nullptr && S.hist_n < S.hist_cap) {
+    const double eta = S_io.eta + (end_of_step ? h : 0.0);
+    int64_t hist_n = S_io.hist_n;
+    if (end_of_step && S_io.hist != nullptr && hist_n < S_io.hist_cap) {
       // total density on this time slice from the first Friedmann equation
       // (2.18): rho = 3 m_pl^2 H^2 with H = a'/a^2 and a' = -p_a/(6 V_L m_pl^2)
       // (eq. (2.14))
-      if (record) {
-        const double hub = -S.p_a * K.inv6VLm2 / (S.a * S.a);
-        double* r = S.hist + kHistRecord * S.hist_n;
-        r[0] = S.eta;
-        r[1] = S.a;
-        r[2] = S.p_a;
-        r[3] = 3.0 * K.mpl2 * hub * hub;
-      }
-      S.hist_n = S.hist_n + 1;
+      const double hub = -pa_end * K.inv6VLm2 / (a_end * a_end);
+      double* r = S_io.hist + kHistRecord * hist_n;
+      r[0] = eta;
+      r[1] = a_end;
+      r[2] = pa_end;
+      r[3] = 3.0 * K.mpl2 * hub * hub;
+      ++hist_n;
     }
-    if (has_next) begin_stage(S, K, w_next, h);
-    if (!(dev_finite(SdD) && dev_finite(SV) && dev_finite(S2) && dev_finite(S.a) &&
-          dev_finite(S.p_a)))
-      S.status |= kStatusNonFinite;
-    S_io = S;
+    out->a = S.a;
+    out->p_a = S.p_a;
+    out->eta = eta;
+    out->S2 = S.S2;
+    out->c_pend = S.c_pend;
+    out->c_next = S.c_next;
+    out->alpha = S.alpha;
+    out->beta = S.beta;
+    out->a_kick = S.a_kick;
+    out->S3_last = K.expand ? S.S3_last : S_io.S3_last;
+    out->parity = S_io.parity ^ 1;
+    out->status = S_io.status | (dev_finite(SdD) && dev_finite(SV) && dev_finite(S2) && dev_finite(S.a) &&
+                                         dev_finite(S.p_a)
+                                     ? 0
+                                     : kStatusNonFinite);
+    out->hist_n = hist_n;
+  } else if (t == kWordHist || t == kWordHist + 1) {
+    reinterpret_cast<word_t*>(out)[t] = word;  // buffer and capacity
+  } else if (K.split ? t >= 64 && t < 64 + 2 * kMaxFields : t >= kWordOffs && t < kScalarWords) {
+    // the offsets the pass wrote around (2 kMaxFields words either way)
+    reinterpret_cast<word_t*>(out)[K.split ? kWordOffs + t - 64 : t] = word;
   }
 }
 
@@ -937,35 +992,30 @@ __device__ __forceinline__ double record_word(const DevScalars* sc, const double
   return 0.0;
 }
 
-// Finish stage (weight w) from the scalars *sc and the pass's partials
-// and offset record, and begin the next (weight w_next) if has_next; eta
-// += h when end_of_step.  The result is in S_io (LDS) once the caller's
-// next barrier has passed; `record` writes the history record (the count
-// advances either way).  The scalar record and the offset record are read
-// by the workgroup together with the partials, so that the serial update
-// of thread 0 waits on no memory.  Contains barriers: all threads call.
-__device__ void stage_update(const DevScalars* sc, const double* partials, const double* offs,
-                             int nblocks, const BgConsts& K, double w, double w_next, double h,
-                             int has_next, int end_of_step, bool record, KSum* scratch,
-                             DevScalars& S_io) {
-  const double word = record_word(sc, offs);
-  KSum v[3] = {{0.0, 0.0}, {0.0, 0.0}, {0.0, 0.0}};
-  for (int b = threadIdx.x; b < nblocks; b += kBlock) {
-    const double* p = partials + size_t(b) * 6;
-#pragma unroll
-    for (int k = 0; k < 3; ++k) v[k] = kcombine(v[k], KSum{p[2 * k], p[2 * k + 1]});
-  }
-  stage_update_finish(word, v, K, w, w_next, h, has_next, end_of_step, record, scratch, S_io);
-}
-
+// Finish stage (weight w) from the scalars *sc_in and the pass's partials and
+// offset record, and begin the next (weight w_next) if has_next; eta += h when
+// end_of_step; write the history record.  The records are read by the
+// workgroup together with the partials, so that the serial update waits on no
+// memory.  Contains a barrier: all threads call.
 __device__ void finalize_body(const DevScalars* sc_in, DevScalars* sc_out, const double* partials,
                               const double* offs, int nblocks, const BgConsts& K, double w,
                               double w_next, double h, int has_next, int end_of_step,
                               KSum* scratch) {
-  __shared__ DevScalars S;
-  stage_update(sc_in, partials, offs, nblocks, K, w, w_next, h, has_next, end_of_step, true,
-               scratch, S);
-  if (threadIdx.x == 0) *sc_out = S;
+  __shared__ DevScalars S_io;
+  const double word = record_word(sc_in, offs);
+  KSum v[3] = {{0.0, 0.0}, {0.0, 0.0}, {0.0, 0.0}};
+  if (int(threadIdx.x) < nblocks) {
+    const double* p = partials + size_t(threadIdx.x) * 6;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) v[k] = KSum{p[2 * k], p[2 * k + 1]};
+  }
+  for (int b = threadIdx.x + kBlock; b < nblocks; b += kBlock) {
+    const double* p = partials + size_t(b) * 6;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) v[k] = kcombine(v[k], KSum{p[2 * k], p[2 * k + 1]});
+  }
+  DevScalars S;
+  stage_update_finish(word, v, K, w, w_next, h, has_next, end_of_step, scratch, S_io, sc_out, S);
 }
 
 static_assert(kChainMaxTiles <= 4 * kBlock, "ChainPre holds four tiles per thread");
@@ -984,29 +1034,49 @@ __device__ void chain_prefetch(const PassParams& P, const Chain& C, ChainPre& cp
   }
 }
 
-template <bool CH>
-__device__ void stage_scalars(const PassParams& P, const Chain& C, int tile_id, DevScalars& S,
-                              KSum* scratch, bool fresh, const ChainPre& cp) {
-  if (!fresh) return;  // S already holds this run's scalars (uniform branch)
+template <bool CH, int NF>
+__device__ __forceinline__ void stage_scalars(const PassParams& P, const Chain& C, int tile_id, DevScalars& S,
+                                              KSum* scratch, bool fresh, const ChainPre& cp, StageIn<NF>& in) {
+  auto take = [&in](const DevScalars& R) {
+    in.c = R.c_next;
+    in.alpha = R.alpha;
+    in.beta = R.beta;
+#pragma unroll
+    for (int i = 0; i < NF; ++i) {
+      in.off_phi[i] = R.off_phi[i];
+      in.off_pi[i] = R.off_pi[i];
+    }
+  };
   if (CH && C.chain) {
     // every workgroup finishes the previous stage the same way (the same
     // partials combined in the same order as stage_update); the first tile
     // keeps the result (and the history record) for the next launch
     KSum v[3] = {{0.0, 0.0}, {0.0, 0.0}, {0.0, 0.0}};
+    if (int(threadIdx.x) < P.ntiles) {
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
+      for (int q = 0; q < 3; ++q) v[q] = KSum{cp.p[0][2 * q], cp.p[0][2 * q + 1]};
+    }
+#pragma unroll
+    for (int k = 1; k < 4; ++k) {
+      if (k * kBlock >= P.ntiles) break;
       if (int(threadIdx.x) + k * kBlock < P.ntiles) {
 #pragma unroll
         for (int q = 0; q < 3; ++q) v[q] = kcombine(v[q], KSum{cp.p[k][2 * q], cp.p[k][2 * q + 1]});
       }
     }
-    stage_update_finish(cp.word, v, P.bg, C.w_prev, C.w, C.h, 1, C.eos, tile_id == 0, scratch, S);
-    if (threadIdx.x == 0 && tile_id == 0) *P.sc[C.s_out] = S;
-  } else if (threadIdx.x < kScalarWords) {
-    reinterpret_cast<word_t*>(&S)[threadIdx.x] =
-        reinterpret_cast<const word_t*>(P.sc[C.s_in])[threadIdx.x];
+    DevScalars N;
+    stage_update_finish(cp.word, v, P.bg, C.w_prev, C.w, C.h, 1, C.eos, scratch, S,
+                        tile_id == 0 ? P.sc[C.s_out] : nullptr, N);
+    take(N);
+    return;
   }
-  __syncthreads();
+  if (fresh) {
+    if (threadIdx.x < kScalarWords)
+      reinterpret_cast<word_t*>(&S)[threadIdx.x] =
+          reinterpret_cast<const word_t*>(P.sc[C.s_in])[threadIdx.x];
+    __syncthreads();
+  }
+  take(S);
 }
 
 __global__ __launch_bounds__(kBlock) void stage_finalize_kernel(const DevScalars* sc_in,
@@ -1076,6 +1146,9 @@ PassParams make_params(const LatView& v) {
   P.ntx = v.tile.ntx;
   P.nty = v.tile.nty;
   P.ntz = v.tile.ntz;
+  P.m_tx = magic_of(v.tile.tx);
+  P.m_ntx = magic_of(v.tile.ntx);
+  P.m_nty = magic_of(v.tile.nty);
   P.zs = v.zs;
   return P;
 }
