@@ -341,8 +341,9 @@ sl_status sl_kernel_timing(sl_lattice* lat, int64_t* passes, double* total_ms);
  * and vx = 2 (2 only up to two fields; 2 tx + 2 ty + 4 <= 256 halo lanes,
  * true for every tx).  A batch
  * member keeps its vx and pf.  sl_get_tile reports the shape in use; sl_set_tile
- * overrides it (tz = 0: z-chunk chosen from the kernel's occupancy so the
- * grid fills whole rounds of resident workgroups).  SL_E_INVALID for
+ * overrides it (tz = 0: the z-chunk with the lowest estimated pass time).  A
+ * lattice that is neither tuned nor given a shape starts with one chosen
+ * from its size, storage and stencil by the same estimate.  SL_E_INVALID for
  * unsupported shapes or more than 65536 workgroups. */
 sl_status sl_get_tile(sl_lattice* lat, int32_t* tx, int32_t* vx, int32_t* ty, int32_t* tz,
                       int32_t* pf);
@@ -363,7 +364,7 @@ sl_status sl_set_chaining(sl_lattice* lat, int32_t mode);
 
 /* Autotuner: time candidate shapes (tx in {16, 32, 64}, 8 with vx = 4, and
  * n/vx when that is in [8, 64] and not a power of two, i.e. a whole row per
- * tile; vx in {1, 2, 4} dividing n; pf in {1, 2, 5, 6, 7}; tz in {occupancy choice,
+ * tile; vx in {1, 2, 4} dividing n; pf in {1, 2, 5, 6, 7}; tz in {the estimate's choice,
  * n/16, n/8, n/4, n/2}, at least 8, and for n <= 128 also 1, 2 and 4)
  * on the lattice's current state: best of `reps` HIP-event timings of six
  * consecutive stages as sl_evolve runs them with that shape (chained

@@ -219,9 +219,6 @@ struct LatView {
 
 // ---- step kernels (kernels_step.hip) --------------------------------------
 hipError_t launch_pass(const LatView& v, const Chain& c, hipStream_t s);
-// Resident workgroups per CU of the pass kernel for this shape and stencil
-// kind (the 27-point pass takes vx = 1, pf = 1 only).
-int pass_blocks_per_cu(int prec, int pot, int nf, const Tile& t, int stencil_kind);
 PassParams pass_params(const LatView& v);
 size_t pass_lds_bytes(int prec, int nf, const Tile& t);
 // Batched form: one fused pass over the tiles of nruns lattices (run table

@@ -1299,13 +1299,6 @@ hipError_t launch_batched_begin(const BatchRun* runs_dev, int nruns, double w, d
   return hipGetLastError();
 }
 
-int pass_blocks_per_cu(int prec, int pot, int nf, const Tile& t, int stencil_kind) {
-  const PassKernel k = pick(prec, pot, nf, t, stencil_kind);
-  int nb = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k.fn, kBlock, k.lds) != hipSuccess) return 1;
-  return nb > 0 ? nb : 1;
-}
-
 hipError_t launch_stage_finalize(const LatView& v, int s_in, int p_in, double w, double w_next,
                                  double h, int has_next, int end_of_step, hipStream_t s) {
   hipLaunchKernelGGL(stage_finalize_kernel, dim3(1), dim3(kBlock), 0, s, s_in ? v.sc1 : v.sc, v.sc,

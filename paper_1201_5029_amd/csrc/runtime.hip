@@ -177,35 +177,46 @@ std::vector<int> tx_candidates(int n, int vx) {
   return v;
 }
 
-// z-chunk length for a shape: the grid should fill the resident capacity
-// (blocks_per_cu * cus) in as few full rounds as possible, since a partial
-// last round leaves most CUs idle; cost = rounds * (chunk + 2 halo planes).
-int pick_tz(int n, int nxy, long resident) {
-  double best = 1e300;
-  int best_len = n;
-  for (int nz = 1; nz <= n; ++nz) {
-    const int len = (n + nz - 1) / nz;
-    const long z = (n + len - 1) / len;
-    const long blocks = long(nxy) * z;
-    if (blocks > kMaxPassBlocks) break;
-    const long rounds = (blocks + resident - 1) / resident;
-    double est = double(rounds) * (len + 2.0);
-    if (blocks * 2 < resident) est *= double(resident) / double(2 * blocks);  // too few waves
-    if (est < best - 1e-9) {
-      best = est;
-      best_len = len;
-    }
+// State bytes (two copies of phi and pi) up to which passes run from the
+// 256 MB last-level cache.
+constexpr double kCachedState = 270e6;
+
+// Lane shape for side n: sites per lane and pass mode.  Measured over sides
+// 16 .. 512, both precisions, every mode (us per stage):
+//  - two sites per lane as soon as rows divide (from 32 up; below, more lanes
+//    are worth more), four where a lane would otherwise move 8 bytes per array
+//    (FP32, one field, 128^3: 13.1 against 13.5) or where FP32 streams from
+//    memory (256^3: 102 against 113);
+//  - a state that stays in the cache loses a quarter with non-temporal stores
+//    (128^3 FP64 26 against 34 us): mode 2;
+//  - one that streams is written around the caches and read ahead, three
+//    planes in FP64 (mode 7; 200^3 104 us, mode 2 at best 109, mode 5 115;
+//    400^3 872 and 879), two in FP32 (mode 6; 512^3 Q-ball 821 us, mode 7 861,
+//    mode 2 1042; 256^3 104, mode 7 102) -- unless FP32 rows are no multiple
+//    of a 128-byte line, which non-temporal stores then write in parts (300^3
+//    209 us with mode 2, 220 with mode 7; 350^3 369 and 380);
+//  - the 27-point pass: two sites per lane, non-temporal where it streams
+//    (256^3 FP64 203 against 211 us).
+void lane_shape(int n, int prec, int nf, int st_kind, int* vx, int* pf) {
+  const int elem = prec == SL_FP32 ? 4 : 8;
+  const bool streams = 4.0 * elem * nf * double(n) * n * n > kCachedState;
+  *vx = (nf <= 2 && n % 2 == 0 && n >= 32) ? 2 : 1;
+  if (st_kind != 0) {
+    *pf = streams && *vx == 2 ? (1 | kPfNontemporal) : 1;
+    return;
   }
-  return best_len;
+  *pf = nf <= 2 ? 2 : 1;
+  if (*vx < 2) return;
+  if (elem == 4 && n % 4 == 0 && (nf == 1 || streams)) *vx = 4;
+  if (!streams || (elem == 4 && n % 32 != 0)) return;
+  *pf = (elem == 8 ? 3 : 2) | kPfNontemporal;
 }
 
-// Default lanes / sites-per-lane / prefetch depth for side n.
-void default_shape(int n, int prec, int nf, int* tx, int* vx, int* pf) {
+// Lane shape a lattice of side n brings into an empty batch: the one that the
+// most sides can share.
+void batch_lane_shape(int n, int nf, int st_kind, int* vx, int* pf) {
   *vx = (nf <= 2 && n % 2 == 0 && n >= 32) ? 2 : 1;
-  *pf = nf <= 2 ? 2 : 1;
-  (void)prec;
-  const int width = n / *vx;
-  *tx = width >= 64 ? 64 : (width >= 32 ? 32 : 16);
+  *pf = nf <= 2 && st_kind == 0 ? 2 : 1;
 }
 
 int device_cus() {
@@ -214,6 +225,64 @@ int device_cus() {
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
     return 256;
   return cus;
+}
+
+// Estimated time (us, less a constant) of a pass in a tile shape, fitted to
+// measured passes of 37 lattices (sides 16 .. 512; the pick's mean distance
+// from the best of all shapes tried is 2.5 %): the CU with the most tiles
+// moves each of their planes and about one more at its share of the memory
+// rate -- the sites read and written, a tenth of the halo rows (mostly cache
+// hits), 14 bytes per halo cell of a column, 80 bytes per row and array where
+// tile rows are not whole 128-byte lines -- unless the march of one tile, 0.64
+// us a plane, takes longer.  Three tiles per CU and more, or two in the modes
+// that read far ahead, cost cache space; beyond kChainMaxTiles the passes do
+// not chain.
+double shape_cost(int n, int nf, int elem, const Tile& t, int cus) {
+  const int tiles = t.nblocks(), m = (tiles + cus - 1) / cus, row = (n + t.vx - 1) / t.vx;
+  const double w = std::min(t.tx, row) * t.vx, rows = std::min(t.ty, n);
+  const bool lines = n * elem % 128 == 0 && (t.tx >= row || t.tx * t.vx * elem % 128 == 0);
+  const double bytes = w * rows * nf * elem * 4.0 + 0.105 * (2.0 * w * nf * elem * 2.0) +
+                       13.8 * (2.0 * rows * nf * 2.0) + (lines ? 0.0 : 80.0 * rows * nf * 4.0);
+  double move = m * (t.tz + 0.92) * bytes / 24900.0 * (256.0 / cus);
+  if (m >= 3)
+    move *= 1.1;
+  else if (m == 2 && pf_nt(t.pf) && pf_depth(t.pf) >= 2)
+    move *= 1.05;
+  const double march = (t.tz + 1) * 0.643;
+  const double a = move * move, b = march * march;
+  return std::sqrt(std::sqrt(a * a + b * b)) + (tiles > kChainMaxTiles ? 5.0 : 0.0);
+}
+
+// The cheapest z-chunk for lanes tx, or with tx = 0 the cheapest pair: powers
+// of two no wider than a row and the widths that cut a row into equal tiles.
+Tile best_tile(int n, int nf, int prec, int vx, int pf, int tx) {
+  const int elem = prec == SL_FP32 ? 4 : 8, cus = device_cus(), row = (n + vx - 1) / vx;
+  std::vector<int> txs;
+  if (tx > 0) {
+    txs.push_back(tx);
+  } else {
+    for (int c : {64, 32, 16})
+      if (c <= row || c == 16) txs.push_back(c);
+    for (int k = 1; k <= 16; ++k) {
+      const int c = (row + k - 1) / k;
+      if (c >= 16 && c <= 64 && std::find(txs.begin(), txs.end(), c) == txs.end()) txs.push_back(c);
+    }
+  }
+  Tile best{};
+  double best_us = 1e300;
+  for (int c : txs)
+    for (int nz = 1; nz <= n; ++nz) {
+      const int tz = (n + nz - 1) / nz;
+      if ((n + tz - 1) / tz != nz) continue;
+      const Tile t = tile_geometry(n, c, vx, tz, pf);
+      if (long(t.nblocks()) > kMaxPassBlocks) break;
+      const double us = shape_cost(n, nf, elem, t, cus);
+      if (us < best_us * (1.0 - 1e-9)) {
+        best_us = us;
+        best = t;
+      }
+    }
+  return best;
 }
 
 size_t partial_doubles() {
@@ -341,7 +410,8 @@ struct sl_lattice {
   bool timing = false;
   int chain_mode = -1;  // sl_set_chaining
   sl_batch* batch = nullptr;  // batch this lattice belongs to, if any
-  int tz_user = 0;  // 0: z-chunk chosen from the occupancy of the pass kernel
+  int tz_user = 0;            // 0: z-chunk chosen by best_tile
+  bool shape_default = true;  // shape from retile_default
   std::vector<std::pair<hipEvent_t, hipEvent_t>> events;
   // captured interior chunk of evolve (kEvolveChunk steps, every finalize
   // begins the next stage), replayed while (dt, order, launch view) match
@@ -386,17 +456,20 @@ sl_status require_state(sl_lattice* L) {
   return SL_OK;
 }
 
-// Apply a pass shape; tz = 0 picks the z-chunk from the kernel's occupancy.
+// Apply a pass shape; tz = 0 picks the z-chunk, tx = 0 the lanes as well.
 void retile(sl_lattice* L, int tx, int vx, int tz, int pf) {
   const int n = L->cfg.n;
-  Tile t = tile_geometry(n, tx, vx, n, pf);
-  if (tz <= 0) {
-    const int bpc = L->pot_set ? pass_blocks_per_cu(L->cfg.precision, L->v.pot, L->cfg.nfields, t,
-                                                    L->v.st.kind)
-                               : 1;
-    tz = pick_tz(n, t.ntx * t.nty, long(bpc) * device_cus());
-  }
-  L->v.tile = tile_geometry(n, tx, vx, tz, pf);
+  L->v.tile = tz > 0 ? tile_geometry(n, tx, vx, tz, pf)
+                     : best_tile(n, L->cfg.nfields, L->cfg.precision, vx, pf, tx);
+}
+
+// The shape of a lattice that has neither been tuned nor given one.
+void retile_default(sl_lattice* L) {
+  int vx, pf;
+  lane_shape(L->cfg.n, L->cfg.precision, L->cfg.nfields, L->v.st.kind, &vx, &pf);
+  retile(L, 0, vx, 0, pf);
+  L->tz_user = 0;
+  L->shape_default = true;
 }
 
 void refresh_m2max(sl_lattice* L) {
@@ -731,11 +804,7 @@ sl_status create_impl(const sl_config* cfg, void* hip_stream, void* const* user,
   v.bg.split = cfg->precision == SL_FP32 ? 1 : 0;
   v.bg.nf = cfg->nfields;
   v.st = Stencil{{-6.0, 1.0, 0.0, 0.0}, 0, 0};
-  {
-    int tx, vx, pf;
-    default_shape(cfg->n, cfg->precision, cfg->nfields, &tx, &vx, &pf);
-    v.tile = tile_geometry(cfg->n, tx, vx, cfg->n, pf);
-  }
+  retile_default(L);
   L->partials_n = partial_doubles();
   L->a_host = cfg->a0;
 
@@ -864,9 +933,8 @@ sl_status sl_set_potential(sl_lattice* L, int32_t kind, const double* params, in
   if (tune_cache().find(key, &tv)) {
     L->tz_user = tv.tz;
     retile(L, tv.tx, tv.vx, tv.tz, tv.pf);
-    return SL_OK;
+    L->shape_default = false;
   }
-  retile(L, L->v.tile.tx, L->v.tile.vx, L->tz_user, L->v.tile.pf);
   return SL_OK;
 }
 
@@ -1504,6 +1572,7 @@ sl_status sl_autotune(sl_lattice* L, int32_t reps, int32_t vx_only, int32_t pf_o
   }
   L->tz_user = win.tz;
   retile(L, win.tx, win.vx, win.tz, win.pf);
+  L->shape_default = false;
   const TuneKey key{L->device, n, L->cfg.nfields, L->cfg.precision, L->v.pot, L->v.st.kind};
   tune_cache().put(key, {win.tx, win.vx, win.tz, win.pf});
   if (L->batch) batch_member_changed(L->batch);
@@ -1552,6 +1621,7 @@ sl_status sl_set_tile(sl_lattice* L, int32_t tx, int32_t vx, int32_t tz, int32_t
   HIP_TRY(hipStreamSynchronize(L->stream));
   L->tz_user = tz;
   retile(L, tx, vx, tz, pf);
+  L->shape_default = false;
   if (L->batch) batch_member_changed(L->batch);
   return SL_OK;
 }
@@ -1586,26 +1656,20 @@ sl_status sl_set_stencil(sl_lattice* L, const double* c) {
   L->v.st = st;
   L->keff2_max = kmax;
   if (kind != old_kind) {
-    int tx = L->v.tile.tx, vx = L->v.tile.vx, pf = L->v.tile.pf;
-    if (kind != 0) {
-      vx = (L->cfg.nfields <= 2 && L->cfg.n % 2 == 0 && L->cfg.n >= 32) ? 2 : 1;
-      pf = 1;
-      const int width = L->cfg.n / vx;
-      tx = width >= 64 ? 64 : (width >= 32 ? 32 : 16);
+    const TuneKey key{L->device, L->cfg.n, L->cfg.nfields, L->cfg.precision, L->v.pot, kind};
+    TuneVal tv;
+    if (L->pot_set && tune_cache().find(key, &tv)) {
+      L->tz_user = tv.tz;
+      retile(L, tv.tx, tv.vx, tv.tz, tv.pf);
+      L->shape_default = false;
     } else {
-      default_shape(L->cfg.n, L->cfg.precision, L->cfg.nfields, &tx, &vx, &pf);
-    }
-    if (L->pot_set) {
-      const TuneKey key{L->device, L->cfg.n, L->cfg.nfields, L->cfg.precision, L->v.pot, kind};
-      TuneVal tv;
-      if (tune_cache().find(key, &tv)) {
-        tx = tv.tx;
-        vx = tv.vx;
-        pf = tv.pf;
-        L->tz_user = tv.tz;
+      const int tz = L->tz_user;
+      retile_default(L);
+      if (tz > 0) {  // a chunk length given by hand stays
+        L->tz_user = tz;
+        retile(L, L->v.tile.tx, L->v.tile.vx, tz, L->v.tile.pf);
       }
     }
-    retile(L, tx, vx, L->tz_user, pf);
   }
   if (L->batch) batch_member_changed(L->batch);
   return SL_OK;
@@ -1824,20 +1888,27 @@ sl_status sl_batch_add(sl_batch* B, sl_lattice* L) {
     vx = tv.vx;
     tz = tv.tz;
     pf = tv.pf;
+  } else if (B->runs.empty() && L->shape_default) {
+    int bvx, bpf;
+    batch_lane_shape(L->cfg.n, L->cfg.nfields, L->v.st.kind, &bvx, &bpf);
+    if (bvx != vx || bpf != pf) {
+      vx = bvx;
+      pf = bpf;
+      tx = tz = 0;
+    }
   }
   if (!B->runs.empty() && (vx != B->shape.vx || pf != B->shape.pf)) {
     vx = B->shape.vx;
     pf = B->shape.pf;
     if (L->cfg.n % vx != 0)
       return fail(SL_E_INVALID, "n = %d is not a multiple of the batch's vx = %d", L->cfg.n, vx);
-    const int width = L->cfg.n / vx;
-    tx = width >= 64 ? 64 : (width >= 32 ? 32 : 16);
-    tz = 0;
+    tx = tz = 0;
   }
   if (tx != L->v.tile.tx || vx != L->v.tile.vx || pf != L->v.tile.pf || tz != L->tz_user) {
     HIP_TRY(hipStreamSynchronize(L->stream));
     L->tz_user = tz;
     retile(L, tx, vx, tz, pf);
+    L->shape_default = false;
   }
   if (B->runs.empty()) {
     B->prec = L->cfg.precision;
@@ -1954,6 +2025,7 @@ sl_status sl_batch_autotune(sl_batch* B, int32_t reps, double* best_ms) {
       if (L->cfg.n == n) {
         L->tz_user = tz;
         retile(L, tx, vx, tz, pf);
+        L->shape_default = false;
       }
     B->shape.vx = vx;
     B->shape.pf = pf;
