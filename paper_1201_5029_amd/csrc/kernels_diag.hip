@@ -15,6 +15,12 @@ constexpr int kDiagBlocksMax = 1024;
 // the largest count, the most that n = 1024 makes)
 constexpr int kDiagTiles = 512;
 
+// Compile-time index of one of two register sets.
+template <int I>
+struct Half {
+  static constexpr int value = I;
+};
+
 struct Bufs {
   const void* phi[2];
   const void* pi[2];
@@ -155,25 +161,50 @@ __global__ __launch_bounds__(kBlock) void energies_kernel(Bufs B, const DevScala
 }
 
 // The same sums for the 7-point stencil, walked like the fused pass: a
-// workgroup owns a kEX x kEY column tile (one wavefront per row) and marches
-// tz planes up in z.  Each lane keeps the drifted field of its site at z-1,
-// z, z+1 in registers; plane z goes to LDS (double-buffered, one barrier per
-// plane) with a one-cell periodic ring of halo cells that designated lanes
-// load, so every plane of the tile is read from memory once.  The loads run
-// one plane ahead of the arithmetic (own column two planes ahead, halo one).
-// Per site the terms and their order are those of energies_kernel; a lane
-// adds its sites' terms plainly over the chunk (at most tz of each) and the
-// lanes' and tiles' totals are combined with compensation.
+// workgroup owns a column tile (one wavefront per row, VX sites per lane) and
+// marches tz planes up in z.  Plane z goes to LDS (double-buffered, one barrier
+// per plane) with the row above the tile and the column right of it, which
+// designated lanes load.  Each bond is visited once, from its lower end: over
+// the periodic lattice sum_x G = sum of (f(x + e) - f(x))^2 over the three
+// forward neighbours, and sum_x f D f = -sum_x G, so neither the other three
+// neighbours nor D are formed (and f D f, whose terms are of the order of f^2
+// times a rounding error, is not summed).  The kernel is bound by
+// instructions: with all six neighbours and D a read-out took 196 us at 256^3
+// in FP64 with two fields and 143 us in FP32, whatever the loads' distance; now
+// 155 and 112 us (about 40 us of each is the launches and the copy back), and
+// 1025 -> 825 us at 512^3 q-ball.
+// The loads run two planes ahead of the arithmetic, in two register sets used
+// in turn.  A lane adds its sites' terms plainly over the chunk and the lanes'
+// and tiles' totals are combined with compensation.
 constexpr int kEX = 64, kEY = kBlock / kEX;
-constexpr int kELX = kEX + 2, kEPlane = kELX * (kEY + 2);
 
-template <typename T, int NF, int KIND>
+template <typename T, int VX>
+struct SiteVec {
+  double v[VX];
+};
+
+template <typename T, int VX>
+__device__ __forceinline__ SiteVec<T, VX> load_sites(const T* __restrict__ p) {
+  static_assert(VX == 1 || sizeof(T) == 8, "");
+  SiteVec<T, VX> r;
+  if constexpr (VX == 1) {
+    r.v[0] = double(p[0]);
+  } else {
+    const double2 q = *reinterpret_cast<const double2*>(p);
+    r.v[0] = q.x;
+    r.v[1] = q.y;
+  }
+  return r;
+}
+
+template <typename T, int NF, int KIND, int VX>
 __global__ __launch_bounds__(kBlock) void energies7_kernel(Bufs B, const DevScalars* sc,
                                                           PotArgs prm, int n, int zs, int tz,
                                                           double* partials) {
   constexpr int NV = nsums<NF>();
+  constexpr int W = kEX * VX, LW = W + VX;  // sites of a tile row; LDS row
   __shared__ KSum scratch[4 * NV];
-  __shared__ double lds[2][NF][kEPlane];
+  __shared__ double lds[2][NF][LW * (kEY + 1)];
   const int par = sc->parity;
   const T* __restrict__ phi = static_cast<const T*>(B.phi[par]);
   const T* __restrict__ pi = static_cast<const T*>(B.pi[par]);
@@ -183,147 +214,171 @@ __global__ __launch_bounds__(kBlock) void energies7_kernel(Bufs B, const DevScal
   for (int i = 0; i < kMaxFields; ++i) pot.p[i] = prm.p[i];
   const size_t n2 = size_t(n) * n;
   // offsets of the stored remainders (0 in FP64 storage), drifted by c
-  double offp[NF], offq[NF];
+  double offp[NF], offq[NF], shift[NF];
 #pragma unroll
   for (int i = 0; i < NF; ++i) {
     offq[i] = sc->off_pi[i];
     offp[i] = sc->off_phi[i] + c * offq[i];
+    shift[i] = offp[i] + fma(c, double(pi[i * n2]), double(phi[i * n2]));
   }
-  double shift[NF];
-#pragma unroll
-  for (int i = 0; i < NF; ++i) shift[i] = offp[i] + fma(c, double(pi[i * n2]), double(phi[i * n2]));
 
-  const int ntx = (n + kEX - 1) / kEX, nty = (n + kEY - 1) / kEY;
+  const int ntx = (n + W - 1) / W, nty = (n + kEY - 1) / kEY;
   int b = blockIdx.x;
   const int xt = b % ntx;
   b /= ntx;
   const int yt = b % nty;
   const int zt = b / nty;
-  const int x0 = xt * kEX, y0 = yt * kEY, z0 = zt * tz;
-  const int wx = min(kEX, n - x0), wy = min(kEY, n - y0), zend = min(z0 + tz, n);
+  const int x0 = xt * W, y0 = yt * kEY, z0 = zt * tz;
+  const int wx = min(W, n - x0), wy = min(kEY, n - y0), zend = min(z0 + tz, n);
   const int tid = int(threadIdx.x), tx = tid % kEX, ty = tid / kEX;
-  const bool active = tx < wx && ty < wy;
-  const int own = (ty + 1) * kELX + tx + 1;
+  const bool active = tx * VX < wx && ty < wy;
+  const int own = ty * LW + tx * VX;
   // every lane issues the same loads (idle lanes read the tile's first
   // column, in range and unused), so that no branch around them makes the
   // compiler wait for the loads in flight
-  const size_t r = active ? size_t(y0 + ty) * n + (x0 + tx) : size_t(y0) * n + x0;
+  const unsigned r = active ? unsigned(y0 + ty) * n + (x0 + tx * VX) : unsigned(y0) * n + x0;
 
-  // halo job: the rows above and below, the columns left and right
-  bool hjob = false;
-  int hl = 0;
-  size_t hr = r;
+  // halo job: the row above (VX sites), the column right of the tile (the
+  // first site of its group; VX divides n)
+  int hjob = 0, hl = 0;
+  unsigned hr = r;
   if (tid < kEX) {
-    if (tid < wx) { hjob = true; hr = size_t((y0 - 1 + n) % n) * n + x0 + tid; hl = tid + 1; }
-  } else if (tid < 2 * kEX) {
-    const int t = tid - kEX;
-    if (t < wx) {
-      hjob = true;
-      hr = size_t((y0 + wy) % n) * n + x0 + t;
-      hl = (wy + 1) * kELX + t + 1;
+    if (tid * VX < wx) {
+      hjob = VX;
+      hr = unsigned(y0 + wy == n ? 0 : y0 + wy) * n + x0 + tid * VX;
+      hl = wy * LW + tid * VX;
     }
-  } else if (tid < 2 * kEX + kEY) {
-    const int q = tid - 2 * kEX;
-    if (q < wy) { hjob = true; hr = size_t(y0 + q) * n + (x0 - 1 + n) % n; hl = (q + 1) * kELX; }
-  } else if (tid < 2 * kEX + 2 * kEY) {
-    const int q = tid - 2 * kEX - kEY;
+  } else if (tid < kEX + kEY) {
+    const int q = tid - kEX;
     if (q < wy) {
-      hjob = true;
-      hr = size_t(y0 + q) * n + (x0 + wx) % n;
-      hl = (q + 1) * kELX + wx + 1;
+      hjob = 1;
+      hr = unsigned(y0 + q) * n + (x0 + wx == n ? 0 : x0 + wx);
+      hl = q * LW + wx;
     }
   }
 
-  auto wrapz = [n](int zz) { return zz < 0 ? zz + n : (zz >= n ? zz - n : zz); };
-  // remainders of phi and pi at one site
-  auto load = [&](int zz, int i, size_t rr, double& p) {
-    const size_t o = (size_t(zz) * zs + i) * n2 + rr;
-    p = double(pi[o]);
-    return double(phi[o]);
-  };
-
+  auto wrapz = [n](int zz) { return zz >= n ? zz - n : zz; };
   double part[NV];
 #pragma unroll
   for (int k = 0; k < NV; ++k) part[k] = 0.0;
-  // drifted field at z-1, z, z+1 and momenta at z, z+1 of the own site;
-  // drifted halo cell of plane z
-  double fm[NF], fc[NF], fp[NF], pc[NF], pp[NF], hc[NF];
-#pragma unroll
-  for (int i = 0; i < NF; ++i) {
-    double p = 0.0;
-    const double f = load(wrapz(z0 - 1), i, r, p);
-    fm[i] = offp[i] + fma(c, p, f);
-    const double g = load(z0, i, r, pc[i]);
-    fc[i] = offp[i] + fma(c, pc[i], g);
-    pc[i] = offq[i] + pc[i];
-    const double h = load(wrapz(z0 + 1), i, r, pp[i]);
-    fp[i] = offp[i] + fma(c, pp[i], h);
-    pp[i] = offq[i] + pp[i];
-    const double hh = load(z0, i, hr, p);
-    hc[i] = offp[i] + fma(c, p, hh);
-  }
-  int buf = 0;
-  for (int z = z0; z < zend; ++z) {
-    // next iteration's loads; past the chunk end they re-read the last
-    // plane they need (in range, unused)
-    double fn[NF], pn[NF], hn[NF], hq[NF];
-    const int z1 = min(z + 1, zend - 1), z2 = wrapz(min(z + 2, zend));
+  // drifted field at z, z+1 and momenta at z of the own sites; drifted halo
+  // of plane z
+  double fc[NF][VX], fp[NF][VX], pc[NF][VX], pp[NF][VX], hc[NF][VX];
+  // loads in flight: remainders and momenta of the own sites and the halo
+  struct Flight {
+    SiteVec<T, VX> f[NF], p[NF], h[NF], q[NF];
+  };
+  auto load_own = [&](int zz, Flight& F) {
 #pragma unroll
     for (int i = 0; i < NF; ++i) {
-      fn[i] = load(z2, i, r, pn[i]);
-      hn[i] = load(z1, i, hr, hq[i]);
+      const size_t o = (size_t(zz) * zs + i) * n2;
+      F.f[i] = load_sites<T, VX>(phi + o + r);
+      F.p[i] = load_sites<T, VX>(pi + o + r);
     }
+  };
+  auto load_halo = [&](int zz, Flight& F) {
 #pragma unroll
     for (int i = 0; i < NF; ++i) {
-      if (active) lds[buf][i][own] = fc[i];
-      if (hjob) lds[buf][i][hl] = hc[i];
+      const size_t o = (size_t(zz) * zs + i) * n2;
+      F.h[i] = load_sites<T, VX>(phi + o + hr);
+      F.q[i] = load_sites<T, VX>(pi + o + hr);
+    }
+  };
+  auto take_own = [&](const Flight& F) {
+#pragma unroll
+    for (int i = 0; i < NF; ++i)
+#pragma unroll
+      for (int v = 0; v < VX; ++v) {
+        fp[i][v] = offp[i] + fma(c, F.p[i].v[v], F.f[i].v[v]);
+        pp[i][v] = offq[i] + F.p[i].v[v];
+      }
+  };
+  auto take_halo = [&](const Flight& F) {
+#pragma unroll
+    for (int i = 0; i < NF; ++i)
+#pragma unroll
+      for (int v = 0; v < VX; ++v) hc[i][v] = offp[i] + fma(c, F.q[i].v[v], F.h[i].v[v]);
+  };
+  auto shift_planes = [&]() {
+#pragma unroll
+    for (int i = 0; i < NF; ++i)
+#pragma unroll
+      for (int v = 0; v < VX; ++v) {
+        fc[i][v] = fp[i][v];
+        pc[i][v] = pp[i][v];
+      }
+  };
+  Flight fl[2];
+  // loads of own plane zz + 2 and halo plane zz + 1; past the chunk end they
+  // re-read the last planes (in range, unused)
+  auto issue = [&](int zz, Flight& F) {
+    load_own(wrapz(min(zz + 2, zend)), F);
+    load_halo(min(zz + 1, zend - 1), F);
+  };
+  load_own(z0, fl[0]);
+  load_halo(z0, fl[0]);
+  load_own(wrapz(z0 + 1), fl[1]);
+  take_own(fl[0]);
+  take_halo(fl[0]);
+  shift_planes();
+  issue(z0, fl[0]);
+  take_own(fl[1]);
+  // plane z: the next plane's loads go out into the other set, this plane's
+  // (set H) are taken at the end
+  auto plane = [&](auto set, int z) {
+    constexpr int H = decltype(set)::value;
+    issue(z + 1, fl[1 - H]);
+#pragma unroll
+    for (int i = 0; i < NF; ++i) {
+      if (active) {
+#pragma unroll
+        for (int v = 0; v < VX; ++v) lds[H][i][own + v] = fc[i][v];
+      }
+      if (hjob == VX) {
+#pragma unroll
+        for (int v = 0; v < VX; ++v) lds[H][i][hl + v] = hc[i][v];
+      } else if (hjob) {
+        lds[H][i][hl] = hc[i][0];
+      }
     }
     __syncthreads();
     if (active) {
-      double f[NF];
 #pragma unroll
-      for (int i = 0; i < NF; ++i) {
-        const double* L = lds[buf][i];
-        const double fcv = fc[i];
-        // neighbours in the order x-1, x+1, y-1, y+1, z-1, z+1
-        const double nb[6] = {L[own - 1], L[own + 1], L[own - kELX], L[own + kELX], fm[i], fp[i]};
-        double D = -6.0 * fcv, G = 0.0;
+      for (int v = 0; v < VX; ++v) {
+        double f[NF];
 #pragma unroll
-        for (int q = 0; q < 6; ++q) {
-          D += nb[q];
-          const double d = nb[q] - fcv;
-          G += d * d;
+        for (int i = 0; i < NF; ++i) {
+          const double* L = lds[H][i] + own + v;
+          const double fcv = fc[i][v];
+          const double dx = (v + 1 < VX ? fc[i][v + 1 < VX ? v + 1 : v] : L[1]) - fcv;
+          const double dy = L[LW] - fcv, dz = fp[i][v] - fcv;
+          part[5 * i + 0] = fma(pc[i][v], pc[i][v], part[5 * i + 0]);
+          part[5 * i + 1] += fma(dx, dx, fma(dy, dy, dz * dz));
+          const double ds = fcv - shift[i];
+          part[5 * i + 2] += ds;
+          part[5 * i + 3] = fma(ds, ds, part[5 * i + 3]);
+          f[i] = fcv;
         }
-        G = 0.5 * G;
-        part[5 * i + 0] += pc[i] * pc[i];
-        part[5 * i + 1] += G;
-        const double ds = fcv - shift[i];
-        part[5 * i + 2] += ds;
-        part[5 * i + 3] += ds * ds;
-        part[5 * i + 4] += fcv * D;
-        f[i] = fcv;
+        double V, dV[NF];
+        potential<KIND, NF, double>(f, pot, V, dV);
+        part[5 * NF] += V;
       }
-      double V, dV[NF];
-      potential<KIND, NF, double>(f, pot, V, dV);
-      part[5 * NF] += V;
     }
-#pragma unroll
-    for (int i = 0; i < NF; ++i) {
-      fm[i] = fc[i];
-      fc[i] = fp[i];
-      pc[i] = pp[i];
-      fp[i] = offp[i] + fma(c, pn[i], fn[i]);
-      pp[i] = offq[i] + pn[i];
-      hc[i] = offp[i] + fma(c, hq[i], hn[i]);
-    }
-    buf ^= 1;
+    shift_planes();
+    take_own(fl[H]);
+    take_halo(fl[H]);
+  };
+  int z = z0;
+  for (; z + 1 < zend; z += 2) {
+    plane(Half<0>{}, z);
+    plane(Half<1>{}, z + 1);
   }
+  if (z < zend) plane(Half<0>{}, z);
+#pragma unroll
+  for (int i = 0; i < NF; ++i) part[5 * i + 4] = -part[5 * i + 1];
   KSum acc[NV];
 #pragma unroll
-  for (int k = 0; k < NV; ++k) {
-    acc[k] = KSum{0.0, 0.0};
-    kadd(acc[k], part[k]);
-  }
+  for (int k = 0; k < NV; ++k) acc[k] = KSum{part[k], 0.0};
   block_reduce<NV>(acc, scratch);
   if (threadIdx.x == 0) {
     double* out = partials + size_t(blockIdx.x) * 2 * NV;
@@ -344,6 +399,19 @@ __global__ __launch_bounds__(kBlock) void energies_finalize(const double* partia
                                                            sl_energies_t* out, int mode) {
   constexpr int NV = nsums<NF>();
   __shared__ KSum scratch[4 * NV];
+  // the scalars and the sums' shift (phi_sync at site 0) are in flight while
+  // the partials are reduced
+  DevScalars S = *sc;
+  double sh[NF];
+#pragma unroll
+  for (int i = 0; i < NF; ++i) {
+    const size_t o = size_t(i) * n * n;
+    const double offp = S.off_phi[i] + S.c_pend * S.off_pi[i];
+    const void *ph = B.phi[S.parity], *pp = B.pi[S.parity];
+    sh[i] = prec == SL_FP32
+                ? offp + fma(S.c_pend, double(static_cast<const float*>(pp)[o]), double(static_cast<const float*>(ph)[o]))
+                : offp + fma(S.c_pend, static_cast<const double*>(pp)[o], static_cast<const double*>(ph)[o]);
+  }
   KSum v[NV];
 #pragma unroll
   for (int k = 0; k < NV; ++k) v[k] = KSum{0.0, 0.0};
@@ -352,39 +420,36 @@ __global__ __launch_bounds__(kBlock) void energies_finalize(const double* partia
 #pragma unroll
     for (int k = 0; k < NV; ++k) v[k] = kcombine(v[k], KSum{p[2 * k], p[2 * k + 1]});
   }
-  block_reduce<NV>(v, scratch);
-  if (threadIdx.x != 0) return;
-  DevScalars S = *sc;
-  double s[NV];
-  for (int k = 0; k < NV; ++k) {
-    s[k] = v[k].s + v[k].c;
-    sums_out[k] = s[k];
+  // a wavefront per quarter of the rows, then one thread per sum
+#pragma unroll
+  for (int k = 0; k < NV; ++k) v[k] = wave_reduce(v[k]);
+  if ((threadIdx.x & 63) == 0) {
+#pragma unroll
+    for (int k = 0; k < NV; ++k) scratch[(threadIdx.x >> 6) * NV + k] = v[k];
   }
-  const size_t n2 = size_t(n) * n;
+  __syncthreads();
+  __shared__ double s[NV];
+  if (threadIdx.x < NV) {
+    KSum t = scratch[threadIdx.x];
+#pragma unroll
+    for (int w = 1; w < kBlock / 64; ++w) t = kcombine(t, scratch[w * NV + threadIdx.x]);
+    s[threadIdx.x] = t.s + t.c;
+    sums_out[threadIdx.x] = s[threadIdx.x];
+  }
+  __syncthreads();
+  if (threadIdx.x != 0) return;
   const double VL = K.VL;
   const double a = S.a;
   const double a2 = a * a, a4 = a2 * a2, a6 = a4 * a2;
   sl_energies_t E;
   for (int i = 0; i < 8; ++i) E.kin[i] = E.grad[i] = E.mean[i] = E.var[i] = 0.0;
   double S2 = 0.0, SdD = 0.0, skin = 0.0, sgrad = 0.0;
-  const int par = S.parity;
+#pragma unroll
   for (int i = 0; i < NF; ++i) {
-    // shift used by the sum kernel: phi_sync at site 0
-    double sh;
-    const double offp = S.off_phi[i] + S.c_pend * S.off_pi[i];
-    if (prec == SL_FP32) {
-      const float* ph = static_cast<const float*>(B.phi[par]);
-      const float* pp = static_cast<const float*>(B.pi[par]);
-      sh = offp + fma(S.c_pend, double(pp[i * n2]), double(ph[i * n2]));
-    } else {
-      const double* ph = static_cast<const double*>(B.phi[par]);
-      const double* pp = static_cast<const double*>(B.pi[par]);
-      sh = offp + fma(S.c_pend, pp[i * n2], ph[i * n2]);
-    }
     E.kin[i] = (s[5 * i] / VL) / (2.0 * a6);
     E.grad[i] = (s[5 * i + 1] / VL) / (2.0 * a2 * K.dx2);
     const double m1 = s[5 * i + 2] / VL;
-    E.mean[i] = sh + m1;
+    E.mean[i] = sh[i] + m1;
     E.var[i] = s[5 * i + 3] / VL - m1 * m1;
     S2 += s[5 * i];
     SdD += s[5 * i + 4];
@@ -437,14 +502,25 @@ hipError_t energies_t(const LatView& v, double* sums, sl_energies_t* out, int mo
   int nb = 0;
   if (v.st.kind == 0) {
     // z-chunks so that the tiles number about kDiagTiles (at most one chunk
-    // per plane)
-    const int cols = ((v.n + kEX - 1) / kEX) * ((v.n + kEY - 1) / kEY);
+    // per plane).  Two sites per lane in FP64 where rows divide, with up to
+    // two fields (registers): 157 us a call at 256^3 with two fields against
+    // 172; in FP32, where a lane's load stays short of 16 bytes, one site is
+    // as fast or faster (111 against 114 us there, 835 against 874 at 512^3
+    // q-ball)
+    const int vx = sizeof(T) == 8 && NF <= 2 && v.n % 2 == 0 ? 2 : 1;
+    const int cols = ((v.n + kEX * vx - 1) / (kEX * vx)) * ((v.n + kEY - 1) / kEY);
     int ntz = kDiagTiles / cols;
     ntz = ntz < 1 ? 1 : (ntz > v.n ? v.n : ntz);
     const int tz = (v.n + ntz - 1) / ntz;
     nb = cols * ((v.n + tz - 1) / tz);
-    hipLaunchKernelGGL((energies7_kernel<T, NF, KIND>), dim3(nb), dim3(kBlock), 0, s, B, v.sc,
-                       v.prm, v.n, v.zs, tz, v.partials);
+    if (vx == 2) {
+      if constexpr (sizeof(T) == 8 && NF <= 2)
+        hipLaunchKernelGGL((energies7_kernel<T, NF, KIND, 2>), dim3(nb), dim3(kBlock), 0, s, B, v.sc,
+                           v.prm, v.n, v.zs, tz, v.partials);
+    } else {
+      hipLaunchKernelGGL((energies7_kernel<T, NF, KIND, 1>), dim3(nb), dim3(kBlock), 0, s, B, v.sc,
+                         v.prm, v.n, v.zs, tz, v.partials);
+    }
   } else {
     nb = int((n3 + kBlock - 1) / kBlock);
     if (nb > kDiagBlocksMax) nb = kDiagBlocksMax;
