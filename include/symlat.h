@@ -305,7 +305,9 @@ sl_status sl_synchronize(sl_lattice* lat);
  * lattice allocates on top while it runs and frees before returning
  * (sl_set_fields / sl_get_fields staging; initial states and spectra work in
  * the field arrays that do not hold the state and allocate only where those
- * are too small, in FP32 storage of one field); 0 if invalid.  Admission keeps footprint + transient free. */
+ * are too small, in FP32 storage of one field); 0 if invalid.  Admission keeps
+ * footprint + transient free.  A lattice also holds pinned host memory for its
+ * read-backs, about 35 n bytes. */
 size_t sl_footprint_bytes(const sl_config* cfg);
 size_t sl_transient_bytes(const sl_config* cfg);
 
@@ -482,7 +484,8 @@ typedef struct sl_linear sl_linear;
  * kx <= n/2 of nfields fields and momenta (2 nfields n^2 (n/2 + 1) complex
  * values, rows padded to 8) and one such array of transform scratch, a copy
  * of the host fields (2 nfields n^3 doubles), and (2 nfields)^2 doubles per
- * mode class (C(n/2 + 3, 3) classes).  SL_E_INVALID for a bad config. */
+ * mode class (C(n/2 + 3, 3) classes).  Pinned host memory: 8 MiB once host
+ * arrays of 8 MiB or more have passed.  SL_E_INVALID for a bad config. */
 sl_status sl_linear_create(const sl_config* cfg, void* hip_stream, sl_linear** out);
 sl_status sl_linear_destroy(sl_linear* lin);
 /* Potential family and parameters, as sl_set_potential. */

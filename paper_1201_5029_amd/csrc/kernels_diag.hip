@@ -171,8 +171,8 @@ __global__ __launch_bounds__(kBlock) void energies_kernel(Bufs B, const DevScala
 // times a rounding error, is not summed).  The kernel is bound by
 // instructions: with all six neighbours and D a read-out took 196 us at 256^3
 // in FP64 with two fields and 143 us in FP32, whatever the loads' distance; now
-// 155 and 112 us (about 40 us of each is the launches and the copy back), and
-// 1025 -> 825 us at 512^3 q-ball.
+// 140 and 94 us (about 25 us of each is the launches and the copy back; before,
+// 40), and 1025 -> 823 us at 512^3 q-ball.
 // The loads run two planes ahead of the arithmetic, in two register sets used
 // in turn.  A lane adds its sites' terms plainly over the chunk and the lanes'
 // and tiles' totals are combined with compensation.

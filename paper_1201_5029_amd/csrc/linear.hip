@@ -29,12 +29,14 @@
 //  * the apply kernel multiplies each Fourier mode by its class's M.
 // All arithmetic is FP64.
 
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <string>
 #include <vector>
 
 #include "fft.h"
+#include "hostio.h"
 #include "timing.h"
 
 namespace symlat {
@@ -476,6 +478,8 @@ struct sl_linear {
   double* means = nullptr;    // 2 nf means and their partial sums
   double2* work = nullptr;    // one half spectrum of transform scratch
   double2* tw = nullptr;      // twiddles and axis table of the transforms
+  ReadBack back;              // background and means on the host
+  HostRing ring;              // host arrays in and out
   int growth_variant = -1;  // columns-per-lane variant, -1 until timed
   bool timing = false;
   // kind 0: one chunk (e0 -> e1 table on the aux stream, e2 -> e3 growth);
@@ -523,8 +527,9 @@ sl_status new_rec(sl_linear* L, int kind, size_t* index) {
 }
 
 sl_status lin_read(sl_linear* L) {
-  HIP_TRY(hipMemcpyAsync(&L->host, L->sc, sizeof(LinScalars), hipMemcpyDeviceToHost, L->stream));
-  HIP_TRY(hipStreamSynchronize(L->stream));
+  const unsigned char* h = nullptr;
+  HIP_TRY(L->back.one(L->sc, sizeof(LinScalars), L->stream, &h));
+  std::memcpy(&L->host, h, sizeof(LinScalars));
   if (!std::isfinite(L->host.a) || !std::isfinite(L->host.p_a))
     return fail(SL_E_NONFINITE, "the background became non-finite");
   return SL_OK;
@@ -563,6 +568,7 @@ sl_status sl_linear_create(const sl_config* cfg, void* hip_stream, sl_linear** o
   if (!L) return fail(SL_E_NOMEM, "host allocation failed");
   L->cfg = *cfg;
   const int n = cfg->n, nf = cfg->nfields;
+  L->back.reserve(std::max(sizeof(LinScalars), 2 * nf * sizeof(double)));
   L->n3 = size_t(n) * n * n;
   L->ncls = class_count(n);
   L->plan = fft_plan(n);
@@ -696,17 +702,18 @@ sl_status sl_linear_set_fields(sl_linear* L, const double* phi, const double* pi
   // host was half of a call at 96^3); nothing of the state changes before
   // they are known to be finite
   const size_t count = size_t(nf) * L->n3;
-  HIP_TRY(hipMemcpyAsync(L->stage, phi, count * sizeof(double), hipMemcpyHostToDevice, L->stream));
-  HIP_TRY(hipMemcpyAsync(L->stage + count, pi, count * sizeof(double), hipMemcpyHostToDevice, L->stream));
+  const HostRange in[2] = {{L->stage, const_cast<double*>(phi), count * sizeof(double)},
+                           {L->stage + count, const_cast<double*>(pi), count * sizeof(double)}};
+  HIP_TRY(L->ring.write(in, 2, L->stream));
   double* part = L->means + 2 * nf;
   hipLaunchKernelGGL(array_sums_kernel, dim3(kMeanBlocks, 2 * nf), dim3(kBlock), 0, L->stream, L->stage, L->n3,
                      part);
   HIP_TRY(hipGetLastError());
   hipLaunchKernelGGL(array_means_kernel, dim3(2 * nf), dim3(64), 0, L->stream, part, double(L->n3), L->means);
   HIP_TRY(hipGetLastError());
-  double mean[2 * kLinMaxFields];
-  HIP_TRY(hipMemcpyAsync(mean, L->means, 2 * nf * sizeof(double), hipMemcpyDeviceToHost, L->stream));
-  HIP_TRY(hipStreamSynchronize(L->stream));
+  const unsigned char* h = nullptr;
+  HIP_TRY(L->back.one(L->means, 2 * nf * sizeof(double), L->stream, &h));
+  const double* mean = reinterpret_cast<const double*>(h);
   for (int i = 0; i < nf; ++i) {
     s.phi0[i] = mean[i];
     s.pi0[i] = mean[nf + i];
@@ -873,9 +880,12 @@ sl_status sl_linear_get_fields(sl_linear* L, double* phi_out, double* pi_out) {
   const double inv = 1.0 / double(L->n3);
   const size_t count = size_t(nf) * L->n3;
   const ModeBuf W = half_spectrum(L, L->work);
+  HostRange out[2];
+  int nout = 0;
   for (int arr = 0; arr < 2; ++arr) {
-    double* out = arr == 0 ? phi_out : pi_out;
-    if (!out) continue;
+    double* host = arr == 0 ? phi_out : pi_out;
+    if (!host) continue;
+    out[nout++] = {L->stage + arr * count, host, count * sizeof(double)};
     const double* zero = arr == 0 ? L->sc->phi0 : L->sc->pi0;  // device addresses
     for (int i = 0; i < nf; ++i) {
       const ModeBuf B = half_spectrum(L, (arr == 0 ? L->dphi : L->dpi) + i * L->modes);
@@ -884,10 +894,8 @@ sl_status sl_linear_get_fields(sl_linear* L, double* phi_out, double* pi_out) {
       HIP_TRY(launch_rows_to_array(L->stage + arr * count + i * L->n3, inv, zero + i, L->plan, W, L->tw,
                                    L->stream));
     }
-    HIP_TRY(hipMemcpyAsync(out, L->stage + arr * count, count * sizeof(double), hipMemcpyDeviceToHost,
-                           L->stream));
   }
-  HIP_TRY(hipStreamSynchronize(L->stream));
+  HIP_TRY(L->ring.read(out, nout, L->stream));
   return SL_OK;
 }
 

@@ -13,6 +13,7 @@
 #include <utility>
 #include <vector>
 
+#include "hostio.h"
 #include "internal.h"
 #include "timing.h"
 
@@ -407,6 +408,7 @@ struct sl_lattice {
   double* hist_dev = nullptr;  // per-step background record (sl_set_history)
   void* fields_mem = nullptr;  // the four field arrays (when the handle owns them)
   void* aux_mem = nullptr;     // scalars, partial sums, sink, observable buffers
+  ReadBack back;               // scalars, energies, spectra on the host
   bool timing = false;
   int chain_mode = -1;  // sl_set_chaining
   sl_batch* batch = nullptr;  // batch this lattice belongs to, if any
@@ -444,9 +446,26 @@ sl_status apply_scalars(sl_lattice* L, const DevScalars& S) {
 }
 
 sl_status read_scalars(sl_lattice* L, DevScalars* S) {
-  HIP_TRY(hipMemcpyAsync(S, L->v.sc, sizeof(DevScalars), hipMemcpyDeviceToHost, L->stream));
-  HIP_TRY(hipStreamSynchronize(L->stream));
+  const unsigned char* h = nullptr;
+  HIP_TRY(L->back.one(L->v.sc, sizeof(DevScalars), L->stream, &h));
+  std::memcpy(S, h, sizeof(DevScalars));
   return apply_scalars(L, *S);
+}
+
+// The scalars behind other results, in one read-back: *h is where the pieces
+// begin.
+sl_status read_with_scalars(sl_lattice* L, ReadBack::Piece first, ReadBack::Piece second,
+                            const char* what, const unsigned char** h) {
+  const ReadBack::Piece p[3] = {first, second, {L->v.sc, sizeof(DevScalars)}};
+  const hipError_t e = L->back.several(p, 3, L->stream, h);
+  if (e != hipSuccess) return fail(SL_E_DEVICE, "%s: %s", what, hipGetErrorString(e));
+  return SL_OK;
+}
+
+sl_status scalars_behind(sl_lattice* L, const unsigned char* h) {
+  DevScalars S;
+  std::memcpy(&S, h, sizeof S);
+  return apply_scalars(L, S);
 }
 
 sl_status require_state(sl_lattice* L) {
@@ -617,24 +636,23 @@ hipError_t transform_rows(sl_lattice* L, int field, int momentum, const SpecScra
 // Field power spectrum in the scratch S; synchronises the lattice's stream.
 sl_status spectrum_run(sl_lattice* L, int field, int nbins, const SpecScratch& S, double* k_out,
                        double* p_out, int64_t* count_out) {
-  std::vector<double> host(size_t(3) * S.nbe);
   hipError_t e = launch_fft_tables(L->cfg.n, L->v.st, S.tw, S.ax, L->stream);
   if (e == hipSuccess) e = transform_rows(L, field, 0, S);
   if (e == hipSuccess)
     e = launch_spectrum_bins(L->v, S.P, S.B, S.tw, S.ax, S.nbe, S.rows, L->spec_dev, L->stream);
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(host.data(), L->spec_dev, host.size() * sizeof(double), hipMemcpyDeviceToHost,
-                       L->stream);
-  if (e == hipSuccess) e = hipStreamSynchronize(L->stream);
   if (e != hipSuccess) return fail(SL_E_DEVICE, "spectrum: %s", hipGetErrorString(e));
+  const size_t count = size_t(3) * S.nbe;
+  const unsigned char* h = nullptr;
+  const sl_status st = read_with_scalars(L, {L->spec_dev, count * sizeof(double)}, {}, "spectrum", &h);
+  if (st != SL_OK) return st;
+  const double* host = reinterpret_cast<const double*>(h);
   for (int k = 0; k < nbins; ++k) {
     const bool own = k < S.nbe;  // no mode reaches the others
     k_out[k] = own ? host[k] : 0.0;
     p_out[k] = own ? host[S.nbe + k] : 0.0;
     count_out[k] = own ? int64_t(host[2 * S.nbe + k]) : 0;
   }
-  DevScalars Sc;
-  return read_scalars(L, &Sc);
+  return scalars_behind(L, reinterpret_cast<const unsigned char*>(host + count));
 }
 
 // Address of this file's `scratch` array on each device, looked up once per
@@ -840,6 +858,8 @@ sl_status create_impl(const sl_config* cfg, void* hip_stream, void* const* user,
       }
     }
   }
+  // the largest read-back: a spectra call's bins, m_eff^2 and the scalars
+  L->back.reserve(sizeof(double) * (5 * size_t(spectrum_bins(cfg->n, kMaxBins)) + 1) + sizeof(DevScalars));
   const AuxLayout aux;
   ok = ok && hipMalloc(&L->aux_mem, aux.total) == hipSuccess;
   if (ok) {
@@ -1246,9 +1266,11 @@ sl_status sl_energies(sl_lattice* L, sl_energies_t* out) {
   if (st != SL_OK) return st;
   if (!out) return fail(SL_E_INVALID, "out is NULL");
   HIP_TRY(launch_energies(L->v, L->sums_dev, L->energies_dev, 0, L->stream));
-  HIP_TRY(hipMemcpyAsync(out, L->energies_dev, sizeof(sl_energies_t), hipMemcpyDeviceToHost, L->stream));
-  DevScalars S;
-  return read_scalars(L, &S);
+  const unsigned char* h = nullptr;
+  st = read_with_scalars(L, {L->energies_dev, sizeof(sl_energies_t)}, {}, "energies", &h);
+  if (st != SL_OK) return st;
+  std::memcpy(out, h, sizeof(sl_energies_t));
+  return scalars_behind(L, h + sizeof(sl_energies_t));
 }
 
 sl_status sl_get_fields(sl_lattice* L, double* phi_out, double* pi_out) {
@@ -1312,8 +1334,6 @@ sl_status sl_spectra(sl_lattice* L, int32_t field, int32_t nbins, double* k_out,
   SpecScratch S;
   st = spec_scratch(L, nbins, 7, nullptr, 0, S);  // 5 sums of the field's pass, 2 of the momentum's
   if (st != SL_OK) return st;
-  std::vector<double> host(size_t(5) * S.nbe);
-  double m2h = 0.0;
   hipError_t e = launch_fft_tables(L->cfg.n, L->v.st, S.tw, S.ax, L->stream);
   if (e == hipSuccess) e = launch_meff(L->v, field, S.mpart, S.m2, L->stream);
   for (int momentum = 0; momentum < 2; ++momentum) {
@@ -1322,11 +1342,12 @@ sl_status sl_spectra(sl_lattice* L, int32_t field, int32_t nbins, double* k_out,
       e = launch_mode_bins(L->v, momentum, S.P, S.B, S.tw, S.ax, S.nbe, S.rows, S.m2, L->stream);
   }
   if (e == hipSuccess) e = launch_mode_bins_finalize(L->v, S.B, S.nbe, S.rows, L->spec_dev, L->stream);
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(host.data(), L->spec_dev, host.size() * sizeof(double), hipMemcpyDeviceToHost, L->stream);
-  if (e == hipSuccess) e = hipMemcpyAsync(&m2h, S.m2, sizeof m2h, hipMemcpyDeviceToHost, L->stream);
-  if (e == hipSuccess) e = hipStreamSynchronize(L->stream);
   if (e != hipSuccess) return fail(SL_E_DEVICE, "spectra: %s", hipGetErrorString(e));
+  const size_t count = size_t(5) * S.nbe;
+  const unsigned char* h = nullptr;
+  st = read_with_scalars(L, {L->spec_dev, count * sizeof(double)}, {S.m2, sizeof(double)}, "spectra", &h);
+  if (st != SL_OK) return st;
+  const double* host = reinterpret_cast<const double*>(h);
   for (int b = 0; b < nbins; ++b) {
     const bool own = b < S.nbe;  // no mode reaches the others
     k_out[b] = own ? host[b] : 0.0;
@@ -1335,9 +1356,8 @@ sl_status sl_spectra(sl_lattice* L, int32_t field, int32_t nbins, double* k_out,
     pn_out[b] = own ? host[3 * S.nbe + b] : 0.0;
     count_out[b] = own ? int64_t(host[4 * S.nbe + b]) : 0;
   }
-  if (m2eff_out) *m2eff_out = m2h;
-  DevScalars Sc;
-  return read_scalars(L, &Sc);
+  if (m2eff_out) *m2eff_out = host[count];
+  return scalars_behind(L, reinterpret_cast<const unsigned char*>(host + count + 1));
 }
 
 sl_status sl_set_chaining(sl_lattice* L, int32_t mode) {
