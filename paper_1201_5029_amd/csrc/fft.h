@@ -26,10 +26,12 @@
 // last stage leaves natural order.  Values pass from thread to thread through
 // one LDS buffer; the first stage reads and the last one writes memory
 // directly.  It is bound by memory: three passes over 8 n^3 bytes.  256^3 in
-// FP64: x pass 118 us from a field and its drift, 78 us from momenta, y pass
-// 51 us (5.6 TB/s); one complex axis pass of a radix-2 transform with a
-// barrier per factor 2 took 266 us, and a direct sum 52 us per axis at 96^3
-// (now 18 + 9 us).
+// FP64: x pass 73 us from a field and its drift (5.5 TB/s), 55 us from momenta,
+// y pass 49 us (5.6 TB/s), four workgroups to a CU; one complex axis pass of a
+// radix-2 transform with a barrier per factor 2 took 266 us, and a direct sum
+// 52 us per axis at 96^3 (now 13 + 8 us).  Loads stay free of branches: with
+// one around the second row of a pair and one around the field of a momentum
+// the x passes took 118 and 78 us.
 #pragma once
 
 #include "device.h"
@@ -345,8 +347,9 @@ hipError_t fft_launch(void (*k)(KArgs...), dim3 grid, int nt, size_t lds, hipStr
 }
 
 // Launch a transform kernel template K<NT, CLS, ...> for a plan: 256 threads
-// up to side 256 (three workgroups per CU), 512 above, so that a group of
-// columns stays a whole 128-byte line up to side 512.
+// up to side 256 (four workgroups per CU; 128 threads up to side 128 took 2-15 %
+// longer at 96 and 128), 512 above, so that a group of columns stays a whole
+// 128-byte line up to side 512.
 #define FFT_DISPATCH(P, LAUNCH)                    \
   do {                                             \
     if ((P).nt == 256) {                           \

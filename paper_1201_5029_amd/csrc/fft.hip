@@ -20,21 +20,22 @@ __global__ void fft_tables_kernel(int n, Stencil st, double2* tw, double* ax) {
 // Rows of one field of a lattice at the synchronised state, less the value at
 // site 0 (a constant moves only the k = 0 mode, which no caller uses, and the
 // rounding of the transform is relative to the largest value): phi + c pi, or
-// the stored momenta.
-template <typename T>
+// the stored momenta.  (Which of them is a template parameter: a branch around
+// the field's load made each value wait for its own.)
+template <typename T, bool MOMENTUM>
 struct LatticeRows {
   const void* phi[2];
   const void* pi[2];
   const DevScalars* sc;
-  int zs, field, momentum;
+  int zs, field;
   struct View {
     const T *f, *p;
     double c, shift;
     size_t n, n2, zs;
-    bool momentum;
     __device__ __forceinline__ double raw(size_t o) const {
       const double q = double(p[o]);
-      return momentum ? q : fma(c, q, double(f[o]));
+      if constexpr (MOMENTUM) return q;
+      return fma(c, q, double(f[o]));
     }
     __device__ __forceinline__ double operator()(int z, int y, int x) const {
       return raw(size_t(z) * zs * n2 + size_t(y) * n + x) - shift;
@@ -49,7 +50,6 @@ struct LatticeRows {
     v.f = static_cast<const T*>(phi[par]) + size_t(field) * v.n2;
     v.p = static_cast<const T*>(pi[par]) + size_t(field) * v.n2;
     v.c = sc->c_pend;
-    v.momentum = momentum != 0;
     v.shift = v.raw(0);
     return v;
   }
@@ -72,7 +72,7 @@ struct ArrayRows {
 
 // Forward x pass: pairs of real rows of `src` into half-spectrum rows.
 template <int NT, int CLS, class Src>
-__global__ __launch_bounds__(NT, NT == 256 ? 3 : 4) void r2c_rows_kernel(FftPlan P, Src src, ModeBuf B,
+__global__ __launch_bounds__(NT, NT == 512 ? 4 : 3) void r2c_rows_kernel(FftPlan P, Src src, ModeBuf B,
                                                       const double2* __restrict__ twg, int lines,
                                                       int npairs) {
   extern __shared__ double2 smem[];
@@ -88,7 +88,9 @@ __global__ __launch_bounds__(NT, NT == 256 ? 3 : 4) void r2c_rows_kernel(FftPlan
     const int cnt = min(lines, npairs - g0);
     auto ld = [&](int l, int e) {
       const int z = div_magic(g0 + l, P.m_hy), y = 2 * (g0 + l - z * hy);
-      return make_double2(S(z, y, e), y + 1 < n ? S(z, y + 1, e) : 0.0);
+      const bool two = y + 1 < n;  // else the row again (no branch around a load)
+      const double a = S(z, y, e), b = S(z, two ? y + 1 : y, e);
+      return make_double2(a, two ? b : 0.0);
     };
     auto none = [](int, int, double2) {};
     fft_lines<NT, CLS, true>(P, M, cnt, buf, tw, ld, none);
@@ -133,7 +135,7 @@ struct ArraySink {
 // the other in its imaginary part.  Z_k for k > n/2 is conj(A_{n-k}) +
 // i conj(B_{n-k}).  Real and imaginary parts exchanged, as in the columns.
 template <int NT, int CLS, class Sink>
-__global__ __launch_bounds__(NT, NT == 256 ? 3 : 4) void c2r_rows_kernel(FftPlan P, ModeBuf B, Sink sink,
+__global__ __launch_bounds__(NT, NT == 512 ? 4 : 3) void c2r_rows_kernel(FftPlan P, ModeBuf B, Sink sink,
                                                       const double2* __restrict__ twg, int lines,
                                                       int npairs) {
   extern __shared__ double2 smem[];
@@ -151,7 +153,9 @@ __global__ __launch_bounds__(NT, NT == 256 ? 3 : 4) void c2r_rows_kernel(FftPlan
       const bool up = 2 * e > n;
       const int k = up ? n - e : e;
       const double2* row = in.at(z) + size_t(y) * P.nhp + k;
-      double2 a = row[0], b = y + 1 < n ? row[P.nhp] : make_double2(0.0, 0.0);
+      const bool two = y + 1 < n;  // else the row again (no branch around a load)
+      double2 a = row[0], b = row[two ? P.nhp : 0];
+      if (!two) b = make_double2(0.0, 0.0);
       if (k == 0 || 2 * k == n) a.y = b.y = 0.0;  // real rows: rounding only
       if (up) {
         a.y = -a.y;
@@ -173,7 +177,7 @@ __global__ __launch_bounds__(NT, NT == 256 ? 3 : 4) void c2r_rows_kernel(FftPlan
 // buffer: in place).  The inverse exchanges real and imaginary parts on the
 // way in and out.
 template <int NT, int CLS>
-__global__ __launch_bounds__(NT, NT == 256 ? 3 : 4) void fft_columns_kernel(FftPlan P, ModeBuf I,
+__global__ __launch_bounds__(NT, NT == 512 ? 4 : 3) void fft_columns_kernel(FftPlan P, ModeBuf I,
                                                          ModeBuf O,
                                                          const double2* __restrict__ twg, int lg,
                                                          int axis, int inverse) {
@@ -257,8 +261,11 @@ int fft_column_lines_log2(const FftPlan& P) {
 }
 
 size_t fft_lds_bytes(int n, int lines) {
+  // the last value's padded place is below v + v/8.  Full groups of 2048
+  // values of side 256 (4096 of side 512) take a quarter (half) of a CU's 160
+  // KB to the byte.
   const size_t v = size_t(lines) * n;
-  return (v + (v >> 3) + 1 + n) * sizeof(double2);
+  return (v + (v >> 3) + n) * sizeof(double2);
 }
 
 hipError_t launch_fft_tables(int n, const Stencil& st, double2* tw, double* ax, hipStream_t s) {
@@ -300,10 +307,10 @@ hipError_t launch_c2r(const FftPlan& P, const ModeBuf& B, const Sink& sink, cons
 #undef C2R_LAUNCH
 }
 
-template <typename T>
-hipError_t r2c_lattice(const LatView& v, int field, int momentum, const FftPlan& P, const ModeBuf& B,
+template <typename T, bool MOMENTUM>
+hipError_t r2c_lattice(const LatView& v, int field, const FftPlan& P, const ModeBuf& B,
                        const double2* tw, hipStream_t s) {
-  LatticeRows<T> src;
+  LatticeRows<T, MOMENTUM> src;
   for (int k = 0; k < 2; ++k) {
     src.phi[k] = v.phi[k];
     src.pi[k] = v.pi[k];
@@ -311,7 +318,6 @@ hipError_t r2c_lattice(const LatView& v, int field, int momentum, const FftPlan&
   src.sc = v.sc;
   src.zs = v.zs;
   src.field = field;
-  src.momentum = momentum;
   return launch_r2c(P, src, B, tw, s);
 }
 
@@ -319,8 +325,11 @@ hipError_t r2c_lattice(const LatView& v, int field, int momentum, const FftPlan&
 
 hipError_t launch_field_rows(const LatView& v, int field, int momentum, const FftPlan& P,
                              const ModeBuf& B, const double2* tw, hipStream_t s) {
-  return v.prec == SL_FP32 ? r2c_lattice<float>(v, field, momentum, P, B, tw, s)
-                           : r2c_lattice<double>(v, field, momentum, P, B, tw, s);
+  if (v.prec == SL_FP32)
+    return momentum ? r2c_lattice<float, true>(v, field, P, B, tw, s)
+                    : r2c_lattice<float, false>(v, field, P, B, tw, s);
+  return momentum ? r2c_lattice<double, true>(v, field, P, B, tw, s)
+                  : r2c_lattice<double, false>(v, field, P, B, tw, s);
 }
 
 hipError_t launch_fft_columns(const FftPlan& P, const ModeBuf& I, const ModeBuf& O, const double2* tw,

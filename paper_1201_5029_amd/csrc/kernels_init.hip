@@ -27,12 +27,13 @@ __device__ __forceinline__ double uniform01(uint64_t seed, uint64_t counter) {
   return (double((x >> 11)) + 1.0) * 0x1.0p-53;
 }
 
+// A normal times sqrt(var): the variance goes under Box-Muller's root.
 __device__ __forceinline__ double normal(uint64_t seed, uint64_t field, uint64_t count,
-                                         uint64_t idx, uint64_t comp) {
+                                         uint64_t idx, uint64_t comp, double var) {
   const uint64_t base = 4ull * (field * count + idx) + 2ull * comp;
   const double u1 = uniform01(seed, base);
   const double u2 = uniform01(seed, base + 1ull);
-  return sqrt(-2.0 * log(u1)) * cospi(2.0 * u2);
+  return sqrt(-2.0 * var * log(u1)) * cospi(2.0 * u2);
 }
 
 template <typename T>
@@ -50,7 +51,7 @@ __global__ void fill_homogeneous_kernel(void* phi0, void* pi0, int nf, int zs, s
 }
 
 struct VacArgs {
-  double L, m2eff, amp, dx2;
+  double m2eff, half_amp2, inv_dx2;  // half_amp2 = A^2/(2 L^3)
   uint64_t seed;
   int field, stencil_kind;
   double stc[4];
@@ -68,7 +69,7 @@ struct VacArgs {
 // y and x passes 12 + 15 us; drawing all n^3 modes took 57 us, the complex
 // axis passes 3 x 27 us and storing the field 8 us.
 template <int NT, int CLS>
-__global__ __launch_bounds__(NT, NT == 256 ? 3 : 4) void vacuum_columns_kernel(
+__global__ __launch_bounds__(NT, NT == 512 ? 4 : 3) void vacuum_columns_kernel(
     FftPlan P, ModeBuf B, const double2* __restrict__ twg, const double* __restrict__ ax, int lg,
     VacArgs A) {
   extern __shared__ double2 smem[];
@@ -79,7 +80,6 @@ __global__ __launch_bounds__(NT, NT == 256 ? 3 : 4) void vacuum_columns_kernel(
   const Modes m = modes_of(B, P);
   const ColMap M{lg};
   const uint64_t n3 = uint64_t(n) * n * n;
-  const double L3 = A.L * A.L * A.L;
   __syncthreads();
   for (int g0 = int(blockIdx.x) * L; g0 < total; g0 += int(gridDim.x) * L) {
     const int id = g0 + (int(threadIdx.x) & (L - 1));
@@ -99,15 +99,15 @@ __global__ __launch_bounds__(NT, NT == 256 ? 3 : 4) void vacuum_columns_kernel(
               ? az + axy + axx
               : -(A.stc[0] + 2.0 * A.stc[1] * (az + axy + axx) +
                   4.0 * A.stc[2] * (az * axy + az * axx + axy * axx) + 8.0 * A.stc[3] * az * axy * axx);
-      const double w2 = keff2 / A.dx2 + A.m2eff;
-      double amp2 = 0.0;
-      if (w2 > 0.0 && e != 0) amp2 = A.amp * A.amp / (2.0 * sqrt(w2) * L3);
-      const double g1 = normal(A.seed, uint64_t(A.field), n3, canon, 0);
-      if (neg == e) return make_double2(0.0, sqrt(amp2) * g1);
-      const double g2 = normal(A.seed, uint64_t(A.field), n3, canon, 1);
-      const double s = sqrt(amp2 / 2.0);
+      const double w2 = fma(keff2, A.inv_dx2, A.m2eff);
+      // E|f|^2, split evenly over two parts unless the mode is real
+      double var = w2 > 0.0 && e != 0 ? A.half_amp2 * rsqrt(w2) : 0.0;
+      if (neg != e) var *= 0.5;
+      const double re = normal(A.seed, uint64_t(A.field), n3, canon, 0, var);
+      if (neg == e) return make_double2(0.0, re);
+      const double im = normal(A.seed, uint64_t(A.field), n3, canon, 1, var);
       // real and imaginary parts exchanged: the forward stages invert
-      return make_double2(e == canon ? s * g2 : -(s * g2), s * g1);
+      return make_double2(e == canon ? im : -im, re);
     };
     auto st = [&](int, int uz, double2 v) {
       if (own) m.at(uz)[idc] = make_double2(v.y, v.x);
@@ -123,7 +123,7 @@ __global__ __launch_bounds__(kBlock) void white_kernel(double* g, size_t n3, int
   KSum acc[1] = {{0.0, 0.0}};
   const size_t stride = size_t(gridDim.x) * blockDim.x;
   for (size_t e = size_t(blockIdx.x) * blockDim.x + threadIdx.x; e < n3; e += stride) {
-    const double v = normal(seed, uint64_t(field), n3, e, 0);
+    const double v = normal(seed, uint64_t(field), n3, e, 0, 1.0);
     g[e] = v;
     kadd(acc[0], v);
   }
@@ -185,11 +185,9 @@ hipError_t launch_vacuum_columns(const LatView& v, int field, double m2eff, doub
                                  const FftPlan& P, const ModeBuf& B, const double2* tw,
                                  const double* ax, hipStream_t s) {
   VacArgs A;
-  const double dx = v.bg.L / v.n;
-  A.L = v.bg.L;
   A.m2eff = m2eff;
-  A.amp = amp;
-  A.dx2 = dx * dx;
+  A.half_amp2 = amp * amp / (2.0 * v.bg.L * v.bg.L * v.bg.L);
+  A.inv_dx2 = v.bg.inv_dx2;
   A.seed = seed;
   A.field = field;
   A.stencil_kind = v.st.kind;

@@ -172,7 +172,7 @@ __device__ void count_modes(int n, int nbe, double* ksum, double* count) {
 // with nothing but the transform; a complex z pass of each and a binning pass
 // over both took 2 x 266 + 391 us.
 template <int NT, int CLS, int KIND>
-__global__ __launch_bounds__(NT, NT == 256 ? 3 : 4) void bin_columns_kernel(FftPlan P, ModeBuf B,
+__global__ __launch_bounds__(NT, NT == 512 ? 4 : 3) void bin_columns_kernel(FftPlan P, ModeBuf B,
                                                          const double2* __restrict__ twg,
                                                          const double* __restrict__ axg, int lg,
                                                          BinArgs A) {
@@ -182,7 +182,7 @@ __global__ __launch_bounds__(NT, NT == 256 ? 3 : 4) void bin_columns_kernel(FftP
   double2* tw = smem;
   double2* buf = smem + n;
   const int vals = L * n;
-  double* ax = reinterpret_cast<double*>(buf + vals + (vals >> 3) + 1);
+  double* ax = reinterpret_cast<double*>(buf + vals + (vals >> 3));
   double* bins = ax + n;
   for (int i = int(threadIdx.x); i < n; i += NT) {
     tw[i] = twg[i];
@@ -253,17 +253,20 @@ __global__ __launch_bounds__(NT, NT == 256 ? 3 : 4) void bin_columns_kernel(FftP
   for (int i = int(threadIdx.x); i < NV * nbe; i += NT) out[i] = bins[i];
 }
 
-// Sum the rows of partial bins: 16 bins per workgroup, 64 threads striding
-// through the rows of each (38 us for 768 rows of 5 + 2 sums, 222 bins; one
-// thread per bin took 100 us for 256 rows of 5); out =
+// Sum the rows of partial bins: kFinBins bins per workgroup, 256 threads striding
+// through the rows of each (17 us for 768 rows of 5 + 2 sums, 222 bins; 38 us
+// with 16 bins to a workgroup, where 14 CUs worked; one thread per bin took 100
+// us for 256 rows of 5); out =
 // [k | <|F|^2> (| <rho> | <n>) | count], nbe values each.  rows2 > 0: rows of
 // the momentum's part follow.
+constexpr int kFinBins = 4;
 template <int NV>
 __global__ __launch_bounds__(1024) void bin_finalize_kernel(ModeBuf B, int rows, int rows2, int nbe,
                                                             double L, double* out) {
-  __shared__ KSum sh[NV][16][16];
-  const int t = int(threadIdx.x), i = t & 15, g = t >> 4, wave = t >> 6;
-  const int b = int(blockIdx.x) * 16 + i;
+  __shared__ KSum sh[NV][16][kFinBins];
+  constexpr int G = 1024 / kFinBins;
+  const int t = int(threadIdx.x), i = t % kFinBins, g = t / kFinBins, wave = t >> 6;
+  const int b = int(blockIdx.x) * kFinBins + i;
   const bool own = b < nbe;
   const double* p1 = B.part[B.sc ? B.sc->parity ^ 1 : 0] + b;
   const double* p2 = p1 + size_t(rows) * NV * nbe;
@@ -272,13 +275,13 @@ __global__ __launch_bounds__(1024) void bin_finalize_kernel(ModeBuf B, int rows,
   for (int q = 0; q < NV; ++q) v[q] = KSum{0.0, 0.0};
   if (own) {
 #pragma unroll 4
-    for (int r = g; r < rows; r += 64) {
+    for (int r = g; r < rows; r += G) {
 #pragma unroll
       for (int q = 0; q < NV; ++q) kadd(v[q], p1[(size_t(r) * NV + q) * nbe]);
     }
     if constexpr (NV == 5) {
 #pragma unroll 4
-      for (int r = g; r < rows2; r += 64) {
+      for (int r = g; r < rows2; r += G) {
         kadd(v[1], p2[size_t(r) * 2 * nbe]);
         kadd(v[2], p2[(size_t(r) * 2 + 1) * nbe]);
       }
@@ -287,16 +290,16 @@ __global__ __launch_bounds__(1024) void bin_finalize_kernel(ModeBuf B, int rows,
 #pragma unroll
   for (int q = 0; q < NV; ++q) {
 #pragma unroll
-    for (int o = 16; o <= 32; o <<= 1) {  // the four row groups of a wavefront
+    for (int o = kFinBins; o <= 32; o <<= 1) {  // the row groups of a wavefront
       KSum w;
       w.s = __shfl_xor(v[q].s, o, 64);
       w.c = __shfl_xor(v[q].c, o, 64);
       v[q] = kcombine(v[q], w);
     }
-    if ((t & 63) < 16) sh[q][wave][i] = v[q];
+    if ((t & 63) < kFinBins) sh[q][wave][i] = v[q];
   }
   __syncthreads();
-  if (t >= 16 || !own) return;
+  if (t >= kFinBins || !own) return;
   double tot[NV];
 #pragma unroll
   for (int q = 0; q < NV; ++q) {
@@ -393,7 +396,7 @@ hipError_t launch_spectrum_bins(const LatView& v, const FftPlan& P, const ModeBu
                                 const double* ax, int nbe, int rows, double* out3, hipStream_t s) {
   const hipError_t e = bin_columns<kBinField>(P, B, tw, ax, rows, bin_args(v, nbe, nullptr), s);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(bin_finalize_kernel<3>, dim3((nbe + 15) / 16), dim3(1024), 0, s, B, rows, 0, nbe, v.bg.L,
+  hipLaunchKernelGGL(bin_finalize_kernel<3>, dim3((nbe + kFinBins - 1) / kFinBins), dim3(1024), 0, s, B, rows, 0, nbe, v.bg.L,
                      out3);
   return hipGetLastError();
 }
@@ -409,7 +412,7 @@ hipError_t launch_mode_bins(const LatView& v, int momentum, const FftPlan& P, co
 
 hipError_t launch_mode_bins_finalize(const LatView& v, const ModeBuf& B, int nbe, int rows, double* out5,
                                      hipStream_t s) {
-  hipLaunchKernelGGL(bin_finalize_kernel<5>, dim3((nbe + 15) / 16), dim3(1024), 0, s, B, rows, rows, nbe, v.bg.L,
+  hipLaunchKernelGGL(bin_finalize_kernel<5>, dim3((nbe + kFinBins - 1) / kFinBins), dim3(1024), 0, s, B, rows, rows, nbe, v.bg.L,
                      out5);
   return hipGetLastError();
 }
