@@ -182,34 +182,52 @@ std::vector<int> tx_candidates(int n, int vx) {
 // 256 MB last-level cache.
 constexpr double kCachedState = 270e6;
 
+// State bytes up to which writing around the caches does no harm (see below).
+constexpr double kSmallState = 12e6;
+
 // Lane shape for side n: sites per lane and pass mode.  Measured over sides
-// 16 .. 512, both precisions, every mode (us per stage):
-//  - two sites per lane as soon as rows divide (from 32 up; below, more lanes
-//    are worth more), four where a lane would otherwise move 8 bytes per array
-//    (FP32, one field, 128^3: 13.1 against 13.5) or where FP32 streams from
-//    memory (256^3: 102 against 113);
-//  - a state that stays in the cache loses a quarter with non-temporal stores
-//    (128^3 FP64 26 against 34 us): mode 2;
-//  - one that streams is written around the caches and read ahead, three
+// 16 .. 512, both precisions, every mode, each in its best tile (us per stage):
+//  - two sites per lane where rows divide, from side 40 up (32^3: one site 4.92,
+//    two 5.53; 40^3 5.68 and 5.52), four where a lane would otherwise move 8
+//    bytes per array (FP32, one field: 56^3 5.05 against 5.23, 128^3 9.95 against
+//    10.98; 48^3 4.95 against 4.79) or where FP32 streams from memory (256^3: 102
+//    against 113);
+//  - in the cache mode 2 (96^3 one field FP64 8.75, mode 1 9.37), but with 16
+//    bytes per site and array, where the deeper pipeline's prologue costs more
+//    than it hides, mode 1 (150^3 38.2, mode 2 40.3; 96^3 13.9 and 14.8; 128^3
+//    level).  Non-temporal stores lose a quarter (128^3 FP64 34 against 26 us),
+//    except in a small state: 48^3 mode 5 5.8, mode 1 5.8, mode 2 6.4, and with
+//    three lattices at a time 2.7, 2.9 and 3.5 each; 64^3 6.7, 7.1, 7.9 alone but
+//    4.5, 4.3, 4.7 of three; 72^3 7.9, 8.5, 9.7 and 6.1, 5.5, 5.8;
+//  - a state that streams is written around the caches and read ahead, three
 //    planes in FP64 (mode 7; 200^3 104 us, mode 2 at best 109, mode 5 115;
 //    400^3 872 and 879), two in FP32 (mode 6; 512^3 Q-ball 821 us, mode 7 861,
 //    mode 2 1042; 256^3 104, mode 7 102) -- unless FP32 rows are no multiple
 //    of a 128-byte line, which non-temporal stores then write in parts (300^3
 //    209 us with mode 2, 220 with mode 7; 350^3 369 and 380);
-//  - the 27-point pass: two sites per lane, non-temporal where it streams
-//    (256^3 FP64 203 against 211 us).
+//  - the 27-point pass: two sites per lane where it streams (non-temporal, 256^3
+//    FP64 203 against 211 us) and with one field (FP64 48^3 5.91 against 6.24,
+//    128^3 15.6 against 16.5, 96^3 11.1 against 10.8); in the cache one site with
+//    two fields (FP64 64^3 9.48 against 10.56, 144^3 38.2 against 40.3; FP32 96^3
+//    12.9 against 14.3), in FP32 up to side 112 (128^3 20.1 against 19.2).
 void lane_shape(int n, int prec, int nf, int st_kind, int* vx, int* pf) {
-  const int elem = prec == SL_FP32 ? 4 : 8;
-  const bool streams = 4.0 * elem * nf * double(n) * n * n > kCachedState;
-  *vx = (nf <= 2 && n % 2 == 0 && n >= 32) ? 2 : 1;
+  const int elem = prec == SL_FP32 ? 4 : 8, site = elem * nf;
+  const double state = 4.0 * site * double(n) * n * n;
+  const bool streams = state > kCachedState;
+  *vx = (nf <= 2 && n % 2 == 0 && n >= 40) ? 2 : 1;
   if (st_kind != 0) {
+    if (!streams && nf == 2 && (elem == 8 || n < 112)) *vx = 1;
     *pf = streams && *vx == 2 ? (1 | kPfNontemporal) : 1;
     return;
   }
   *pf = nf <= 2 ? 2 : 1;
   if (*vx < 2) return;
-  if (elem == 4 && n % 4 == 0 && (nf == 1 || streams)) *vx = 4;
-  if (!streams || (elem == 4 && n % 32 != 0)) return;
+  if (elem == 4 && n % 4 == 0 && (streams || (nf == 1 && n >= 56))) *vx = 4;
+  if (!streams) {
+    if (site == 16) *pf = state <= kSmallState ? (1 | kPfNontemporal) : 1;
+    return;
+  }
+  if (elem == 4 && n % 32 != 0) return;
   *pf = (elem == 8 ? 3 : 2) | kPfNontemporal;
 }
 
@@ -229,34 +247,53 @@ int device_cus() {
 }
 
 // Estimated time (us, less a constant) of a pass in a tile shape, fitted to
-// measured passes of 37 lattices (sides 16 .. 512; the pick's mean distance
-// from the best of all shapes tried is 2.5 %): the CU with the most tiles
-// moves each of their planes and about one more at its share of the memory
-// rate -- the sites read and written, a tenth of the halo rows (mostly cache
-// hits), 14 bytes per halo cell of a column, 80 bytes per row and array where
-// tile rows are not whole 128-byte lines -- unless the march of one tile, 0.64
-// us a plane, takes longer.  Three tiles per CU and more, or two in the modes
-// that read far ahead, cost cache space; beyond kChainMaxTiles the passes do
-// not chain.
-double shape_cost(int n, int nf, int elem, const Tile& t, int cus) {
+// measured passes of 83 lattices (sides 16 .. 512; the pick's mean distance
+// from the best of all shapes tried is 0.6 % in the cache, 2 % beyond): the CU
+// with the most tiles moves each of their planes and a prologue's worth more at
+// its share of the memory rate -- the sites read and written, a tenth of the
+// halo rows (mostly cache hits), the halo cells of a column, some bytes per row
+// and array where tile rows are not whole 128-byte lines -- unless the march of
+// one tile, a fixed time per plane, takes longer.  In the cache the prologue
+// counts for less where the loads run one plane ahead only; three tiles per CU
+// and more cost cache space, and so do two that read far ahead while they
+// stream; a single tile per CU waits for its loads in the modes that run one
+// plane ahead (120^3 FP64, 240 tiles: 26.5 us, 450 tiles 20.3); beyond
+// kChainMaxTiles the passes do not chain.
+struct ShapeFit {
+  double ahead[2];  // planes' worth of a tile's prologue, depth 1 and deeper
+  double halo_cell, ragged;
+  double plane[2], site;  // us of a plane's march: fixed (by depth) and per value of a lane
+  double ends;            // planes' worth of the march's two ends
+  double third;           // factor from three tiles per CU
+};
+constexpr ShapeFit kFitCached = {{0.05, 0.9}, 54.0, 24.0, {0.59, 0.88}, 0.042, 0.63, 1.285};
+constexpr ShapeFit kFitStreams = {{0.92, 0.92}, 13.8, 80.0, {0.643, 0.643}, 0.0, 1.0, 1.1};
+
+double shape_cost(int n, int nf, int elem, int st_kind, const Tile& t, int cus) {
+  const bool streams = 4.0 * elem * nf * double(n) * n * n > kCachedState;
+  const ShapeFit& F = streams ? kFitStreams : kFitCached;
   const int tiles = t.nblocks(), m = (tiles + cus - 1) / cus, row = (n + t.vx - 1) / t.vx;
+  const int deep = pf_depth(t.pf) >= 2 ? 1 : 0, lag = st_kind != 0 && !streams ? 1 : 0;
   const double w = std::min(t.tx, row) * t.vx, rows = std::min(t.ty, n);
   const bool lines = n * elem % 128 == 0 && (t.tx >= row || t.tx * t.vx * elem % 128 == 0);
-  const double bytes = w * rows * nf * elem * 4.0 + 0.105 * (2.0 * w * nf * elem * 2.0) +
-                       13.8 * (2.0 * rows * nf * 2.0) + (lines ? 0.0 : 80.0 * rows * nf * 4.0);
-  double move = m * (t.tz + 0.92) * bytes / 24900.0 * (256.0 / cus);
+  const double bytes = w * rows * nf * elem * 4.0 + 0.104 * (2.0 * w * nf * elem * 2.0) +
+                       F.halo_cell * (2.0 * rows * nf * 2.0) + (lines ? 0.0 : F.ragged * rows * nf * 4.0);
+  double move = m * (t.tz + F.ahead[deep] + lag) * bytes / 24900.0 * (256.0 / cus);
   if (m >= 3)
-    move *= 1.1;
-  else if (m == 2 && pf_nt(t.pf) && pf_depth(t.pf) >= 2)
+    move *= F.third;
+  else if (streams && m == 2 && pf_nt(t.pf) && deep)
     move *= 1.05;
-  const double march = (t.tz + 1) * 0.643;
+  else if (!streams && m == 1 && !deep && st_kind == 0)
+    move *= 1.3;  // no second tile's work to hide the loads behind
+  // the 27-point pass writes a plane behind and does half as much again per site
+  const double march = (t.tz + F.ends + lag) * (F.plane[deep] + F.site * t.vx * nf * (lag ? 1.5 : 1.0));
   const double a = move * move, b = march * march;
   return std::sqrt(std::sqrt(a * a + b * b)) + (tiles > kChainMaxTiles ? 5.0 : 0.0);
 }
 
 // The cheapest z-chunk for lanes tx, or with tx = 0 the cheapest pair: powers
 // of two no wider than a row and the widths that cut a row into equal tiles.
-Tile best_tile(int n, int nf, int prec, int vx, int pf, int tx) {
+Tile best_tile(int n, int nf, int prec, int st_kind, int vx, int pf, int tx) {
   const int elem = prec == SL_FP32 ? 4 : 8, cus = device_cus(), row = (n + vx - 1) / vx;
   std::vector<int> txs;
   if (tx > 0) {
@@ -277,7 +314,7 @@ Tile best_tile(int n, int nf, int prec, int vx, int pf, int tx) {
       if ((n + tz - 1) / tz != nz) continue;
       const Tile t = tile_geometry(n, c, vx, tz, pf);
       if (long(t.nblocks()) > kMaxPassBlocks) break;
-      const double us = shape_cost(n, nf, elem, t, cus);
+      const double us = shape_cost(n, nf, elem, st_kind, t, cus);
       if (us < best_us * (1.0 - 1e-9)) {
         best_us = us;
         best = t;
@@ -479,7 +516,7 @@ sl_status require_state(sl_lattice* L) {
 void retile(sl_lattice* L, int tx, int vx, int tz, int pf) {
   const int n = L->cfg.n;
   L->v.tile = tz > 0 ? tile_geometry(n, tx, vx, tz, pf)
-                     : best_tile(n, L->cfg.nfields, L->cfg.precision, vx, pf, tx);
+                     : best_tile(n, L->cfg.nfields, L->cfg.precision, L->v.st.kind, vx, pf, tx);
 }
 
 // The shape of a lattice that has neither been tuned nor given one.
