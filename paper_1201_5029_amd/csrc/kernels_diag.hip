@@ -9,8 +9,8 @@ namespace symlat {
 namespace {
 
 constexpr int kDiagBlocksMax = 1024;
-// target tile count of the 7-point observables pass: two tiles per CU
-// (measured at 256^3: 2048 and 1024 tiles took 10 % and 6 % longer; a tile
+// target tile count of the observables passes: two tiles per CU
+// (measured at 256^3, 7-point: 1024 tiles took 4-13 % longer; a tile
 // writes 2 nsums doubles of partials and the buffer holds 4096 tiles of
 // the largest count, the most that n = 1024 makes)
 constexpr int kDiagTiles = 512;
@@ -39,128 +39,7 @@ Bufs bufs_of(const LatView& v) {
 template <int NF>
 constexpr int nsums() { return 5 * NF + 1; }
 
-// G[f] and D[f] of eq. (2.7)-(2.8) at one site with the general cubic
-// stencil: the 26 neighbours weighted by class (face, edge, corner).
-template <typename T>
-__device__ void stencil27_at(const T* __restrict__ phi, const T* __restrict__ pi, double c,
-                             double offp, int i, int zs, int n, int x, int y, int z, double f,
-                             const Stencil& st, double& D, double& G) {
-  const size_t n2 = size_t(n) * n;
-  double acc[4] = {0.0, 0.0, 0.0, 0.0}, g[4] = {0.0, 0.0, 0.0, 0.0};
-  for (int dz = -1; dz <= 1; ++dz) {
-    const int zz = z + dz < 0 ? n - 1 : (z + dz >= n ? 0 : z + dz);
-    for (int dy = -1; dy <= 1; ++dy) {
-      const int yy = y + dy < 0 ? n - 1 : (y + dy >= n ? 0 : y + dy);
-      for (int dx = -1; dx <= 1; ++dx) {
-        const int cls = (dz != 0) + (dy != 0) + (dx != 0);
-        if (cls == 0) continue;
-        const int xx = x + dx < 0 ? n - 1 : (x + dx >= n ? 0 : x + dx);
-        const size_t e = (size_t(zz) * zs + i) * n2 + size_t(yy) * n + xx;
-        const double v = offp + fma(c, double(pi[e]), double(phi[e]));
-        acc[cls] += v;
-        const double d = v - f;
-        g[cls] += d * d;
-      }
-    }
-  }
-  D = st.c[0] * f + st.c[1] * acc[1] + st.c[2] * acc[2] + st.c[3] * acc[3];
-  G = 0.5 * (st.c[1] * g[1] + st.c[2] * g[2] + st.c[3] * g[3]);
-}
-
-template <typename T, int NF, int KIND>
-__global__ __launch_bounds__(kBlock) void energies_kernel(Bufs B, const DevScalars* sc,
-                                                         PotArgs prm, int n, int zs, Stencil st,
-                                                         double* partials) {
-  constexpr int NV = nsums<NF>();
-  __shared__ KSum scratch[4 * NV];
-  const int par = sc->parity;
-  const T* __restrict__ phi = static_cast<const T*>(B.phi[par]);
-  const T* __restrict__ pi = static_cast<const T*>(B.pi[par]);
-  const double c = sc->c_pend;
-  PotT<double> pot;
-#pragma unroll
-  for (int i = 0; i < kMaxFields; ++i) pot.p[i] = prm.p[i];
-  const size_t n2 = size_t(n) * n, n3 = n2 * n;
-  // offsets of the stored remainders (0 in FP64 storage), drifted by c
-  double offp[NF], offq[NF];
-#pragma unroll
-  for (int i = 0; i < NF; ++i) {
-    offq[i] = sc->off_pi[i];
-    offp[i] = sc->off_phi[i] + c * offq[i];
-  }
-
-  // field i of plane z starts at (z zs + i) n^2
-  double shift[NF];
-#pragma unroll
-  for (int i = 0; i < NF; ++i) shift[i] = offp[i] + fma(c, double(pi[i * n2]), double(phi[i * n2]));
-
-  KSum acc[NV];
-#pragma unroll
-  for (int k = 0; k < NV; ++k) acc[k] = KSum{0.0, 0.0};
-
-  const size_t stride = size_t(gridDim.x) * blockDim.x;
-  for (size_t e = size_t(blockIdx.x) * blockDim.x + threadIdx.x; e < n3; e += stride) {
-    const int x = int(e % n);
-    const int y = int((e / n) % n);
-    const int z = int(e / n2);
-    const size_t r = e - size_t(z) * n2;  // y n + x
-    const size_t zm = size_t(z == 0 ? n - 1 : z - 1), zp = size_t(z == n - 1 ? 0 : z + 1);
-    // neighbours as (plane, in-plane index)
-    const size_t nz[6] = {size_t(z), size_t(z), size_t(z), size_t(z), zm, zp};
-    const size_t nr[6] = {r - x + (x == 0 ? n - 1 : x - 1), r - x + (x == n - 1 ? 0 : x + 1),
-                          r + (size_t((y == 0 ? n - 1 : y - 1)) - y) * n,
-                          r + (size_t((y == n - 1 ? 0 : y + 1)) - y) * n, r, r};
-    double f[NF];
-#pragma unroll
-    for (int i = 0; i < NF; ++i) {
-      const size_t o = (size_t(z) * zs + i) * n2 + r;
-      const double pr = double(pi[o]);
-      const double pc = offq[i] + pr;
-      const double fcv = offp[i] + fma(c, pr, double(phi[o]));
-      f[i] = fcv;
-      double D, G;
-      if (st.kind == 0) {
-        double nb[6];
-#pragma unroll
-        for (int q = 0; q < 6; ++q) {
-          const size_t on = (nz[q] * zs + i) * n2 + nr[q];
-          nb[q] = offp[i] + fma(c, double(pi[on]), double(phi[on]));
-        }
-        D = -6.0 * fcv;
-        G = 0.0;
-#pragma unroll
-        for (int q = 0; q < 6; ++q) {
-          D += nb[q];
-          const double d = nb[q] - fcv;
-          G += d * d;
-        }
-        G = 0.5 * G;
-      } else {
-        stencil27_at<T>(phi, pi, c, offp[i], i, zs, n, x, y, z, fcv, st, D, G);
-      }
-      kadd(acc[5 * i + 0], pc * pc);
-      kadd(acc[5 * i + 1], G);
-      const double ds = fcv - shift[i];
-      kadd(acc[5 * i + 2], ds);
-      kadd(acc[5 * i + 3], ds * ds);
-      kadd(acc[5 * i + 4], fcv * D);
-    }
-    double V, dV[NF];
-    potential<KIND, NF, double>(f, pot, V, dV);
-    kadd(acc[5 * NF], V);
-  }
-  block_reduce<NV>(acc, scratch);
-  if (threadIdx.x == 0) {
-    double* out = partials + size_t(blockIdx.x) * 2 * NV;
-#pragma unroll
-    for (int k = 0; k < NV; ++k) {
-      out[2 * k] = acc[k].s;
-      out[2 * k + 1] = acc[k].c;
-    }
-  }
-}
-
-// The same sums for the 7-point stencil, walked like the fused pass: a
+// The sums for the 7-point stencil, walked like the fused pass: a
 // workgroup owns a column tile (one wavefront per row, VX sites per lane) and
 // marches tz planes up in z.  Plane z goes to LDS (double-buffered, one barrier
 // per plane) with the row above the tile and the column right of it, which
@@ -390,6 +269,179 @@ __global__ __launch_bounds__(kBlock) void energies7_kernel(Bufs B, const DevScal
   }
 }
 
+// The sums with a general member of the cubic family, walked the same way with
+// one site per lane: 13 forward neighbours stand for the 26, four in the plane
+// and nine in the next, so a plane goes to LDS with a whole ring of halo cells
+// and three planes are kept (one barrier per plane).  With
+// G = 1/2 sum_d c_d (f(x + d) - f(x))^2 and D f = sum_d c_d (f(x + d) - f(x))
+// + rest f, rest = c0 + 6 c1 + 12 c2 + 8 c3 (0 up to rounding),
+// sum_x f D f = -sum_x G + rest sum_x f^2.  It is bound by instructions and
+// LDS reads: a read-out takes 196 us at 256^3 in FP64 with two fields and 140 in
+// FP32 (206 and 156 with 1024 tiles instead of 512); with each site reading 26
+// neighbours and their momenta from memory it took 1054 and 575 us.
+template <typename T, int NF, int KIND>
+__global__ __launch_bounds__(kBlock) void energies27_kernel(Bufs B, const DevScalars* sc,
+                                                           PotArgs prm, int n, int zs, int tz,
+                                                           Stencil st, double* partials) {
+  constexpr int NV = nsums<NF>();
+  constexpr int LX = kEX + 2, P = LX * (kEY + 2);
+  static_assert(2 * kEX + 2 * kEY + 4 <= kBlock, "one halo cell per thread");
+  __shared__ KSum scratch[4 * NV];
+  extern __shared__ double planes[];  // [3][NF][P]
+  const int par = sc->parity;
+  const T* __restrict__ phi = static_cast<const T*>(B.phi[par]);
+  const T* __restrict__ pi = static_cast<const T*>(B.pi[par]);
+  const double c = sc->c_pend;
+  PotT<double> pot;
+#pragma unroll
+  for (int i = 0; i < kMaxFields; ++i) pot.p[i] = prm.p[i];
+  const size_t n2 = size_t(n) * n;
+  // offsets of the stored remainders (0 in FP64 storage), drifted by c
+  double offp[NF], offq[NF], shift[NF];
+#pragma unroll
+  for (int i = 0; i < NF; ++i) {
+    offq[i] = sc->off_pi[i];
+    offp[i] = sc->off_phi[i] + c * offq[i];
+    shift[i] = offp[i] + fma(c, double(pi[i * n2]), double(phi[i * n2]));
+  }
+
+  const int ntx = (n + kEX - 1) / kEX, nty = (n + kEY - 1) / kEY;
+  int b = blockIdx.x;
+  const int xt = b % ntx;
+  b /= ntx;
+  const int yt = b % nty, zt = b / nty;
+  const int x0 = xt * kEX, y0 = yt * kEY, z0 = zt * tz;
+  const int wx = min(kEX, n - x0), wy = min(kEY, n - y0), zend = min(z0 + tz, n);
+  const int tid = int(threadIdx.x), tx = tid % kEX, ty = tid / kEX;
+  const bool active = tx < wx && ty < wy;
+  const int own = (ty + 1) * LX + 1 + tx;
+  // every lane issues the same loads (see above)
+  const unsigned r = active ? unsigned(y0 + ty) * n + (x0 + tx) : unsigned(y0) * n + x0;
+
+  // halo job: one cell of the ring around the tile
+  int hl = -1;
+  unsigned hr = r;
+  {
+    const int xl = x0 == 0 ? n - 1 : x0 - 1, xr = x0 + wx == n ? 0 : x0 + wx;
+    const int yl = y0 == 0 ? n - 1 : y0 - 1, yr = y0 + wy == n ? 0 : y0 + wy;
+    int hx = 0, hy = 0;
+    if (tid < 2 * kEX) {
+      const bool up = tid >= kEX;
+      const int t = up ? tid - kEX : tid;
+      if (t < wx) {
+        hx = x0 + t;
+        hy = up ? yr : yl;
+        hl = (up ? wy + 1 : 0) * LX + 1 + t;
+      }
+    } else if (tid < 2 * kEX + 2 * kEY) {
+      const int q = tid - 2 * kEX;
+      const bool right = q >= kEY;
+      const int t = right ? q - kEY : q;
+      if (t < wy) {
+        hx = right ? xr : xl;
+        hy = y0 + t;
+        hl = (t + 1) * LX + (right ? wx + 1 : 0);
+      }
+    } else if (tid < 2 * kEX + 2 * kEY + 4) {
+      const int q = tid - 2 * kEX - 2 * kEY;
+      hx = (q & 1) ? xr : xl;
+      hy = (q & 2) ? yr : yl;
+      hl = ((q & 2) ? wy + 1 : 0) * LX + ((q & 1) ? wx + 1 : 0);
+    }
+    if (hl >= 0) hr = unsigned(hy) * n + hx;
+  }
+
+  auto wrapz = [n](int zz) { return zz >= n ? zz - n : zz; };
+  double part[NV];
+#pragma unroll
+  for (int k = 0; k < NV; ++k) part[k] = 0.0;
+  double fc[NF], pc[NF], fn[NF], pn[NF];  // own site at z and z + 1
+  T lf[NF], lp[NF], hf[NF], hp[NF];       // loads in flight: own site, halo cell
+  auto issue = [&](int zz) {
+#pragma unroll
+    for (int i = 0; i < NF; ++i) {
+      const size_t o = (size_t(zz) * zs + i) * n2;
+      lf[i] = phi[o + r];
+      lp[i] = pi[o + r];
+      hf[i] = phi[o + hr];
+      hp[i] = pi[o + hr];
+    }
+  };
+  // the plane in flight to LDS buffer k, its own site to fn and pn
+  auto land = [&](int k) {
+#pragma unroll
+    for (int i = 0; i < NF; ++i) {
+      double* L = planes + size_t(k * NF + i) * P;
+      fn[i] = offp[i] + fma(c, double(lp[i]), double(lf[i]));
+      pn[i] = offq[i] + double(lp[i]);
+      if (active) L[own] = fn[i];
+      if (hl >= 0) L[hl] = offp[i] + fma(c, double(hp[i]), double(hf[i]));
+    }
+  };
+  auto next = [&]() {
+#pragma unroll
+    for (int i = 0; i < NF; ++i) {
+      fc[i] = fn[i];
+      pc[i] = pn[i];
+    }
+  };
+  issue(z0);
+  land(0);
+  next();
+  issue(wrapz(z0 + 1));
+  int k0 = 0, count = 0;
+  for (int z = z0; z < zend; ++z) {
+    const int k1 = k0 == 2 ? 0 : k0 + 1;
+    land(k1);
+    __syncthreads();
+    issue(wrapz(min(z + 2, zend)));  // past the chunk's end: in range, unused
+    if (active) {
+      ++count;
+#pragma unroll
+      for (int i = 0; i < NF; ++i) {
+        const double* A = planes + size_t(k0 * NF + i) * P + own;
+        const double* U = planes + size_t(k1 * NF + i) * P + own;
+        const double f = fc[i];
+        auto sq = [f](double v, double s) {
+          const double d = v - f;
+          return fma(d, d, s);
+        };
+        const double faces = sq(fn[i], sq(A[LX], sq(A[1], 0.0)));
+        const double edges = sq(U[LX], sq(U[-LX], sq(U[1], sq(U[-1], sq(A[LX + 1], sq(A[LX - 1], 0.0))))));
+        const double corners = sq(U[LX + 1], sq(U[LX - 1], sq(U[-LX + 1], sq(U[-LX - 1], 0.0))));
+        part[5 * i + 0] = fma(pc[i], pc[i], part[5 * i + 0]);
+        part[5 * i + 1] += fma(st.c[1], faces, fma(st.c[2], edges, st.c[3] * corners));
+        const double ds = f - shift[i];
+        part[5 * i + 2] += ds;
+        part[5 * i + 3] = fma(ds, ds, part[5 * i + 3]);
+      }
+      double V, dV[NF];
+      potential<KIND, NF, double>(fc, pot, V, dV);
+      part[5 * NF] += V;
+    }
+    next();
+    k0 = k1;
+  }
+  const double rest = (st.c[0] + 6.0 * st.c[1]) + (12.0 * st.c[2] + 8.0 * st.c[3]);
+#pragma unroll
+  for (int i = 0; i < NF; ++i) {
+    const double f2 = part[5 * i + 3] + shift[i] * (2.0 * part[5 * i + 2] + shift[i] * count);
+    part[5 * i + 4] = fma(rest, f2, -part[5 * i + 1]);
+  }
+  KSum acc[NV];
+#pragma unroll
+  for (int k = 0; k < NV; ++k) acc[k] = KSum{part[k], 0.0};
+  block_reduce<NV>(acc, scratch);
+  if (threadIdx.x == 0) {
+    double* out = partials + size_t(blockIdx.x) * 2 * NV;
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+      out[2 * k] = acc[k].s;
+      out[2 * k + 1] = acc[k].c;
+    }
+  }
+}
+
 // Reduce energies partials, compute observables; mode 1 also solves the
 // constraint H = 0 for p_a (expanding branch) and sets S2.
 template <int NF>
@@ -498,34 +550,33 @@ __global__ __launch_bounds__(kBlock) void energies_finalize(const double* partia
 template <typename T, int NF, int KIND>
 hipError_t energies_t(const LatView& v, double* sums, sl_energies_t* out, int mode, hipStream_t s) {
   const Bufs B = bufs_of(v);
-  const size_t n3 = size_t(v.n) * v.n * v.n;
-  int nb = 0;
-  if (v.st.kind == 0) {
-    // z-chunks so that the tiles number about kDiagTiles (at most one chunk
-    // per plane).  Two sites per lane in FP64 where rows divide, with up to
-    // two fields (registers): 157 us a call at 256^3 with two fields against
-    // 172; in FP32, where a lane's load stays short of 16 bytes, one site is
-    // as fast or faster (111 against 114 us there, 835 against 874 at 512^3
-    // q-ball)
-    const int vx = sizeof(T) == 8 && NF <= 2 && v.n % 2 == 0 ? 2 : 1;
-    const int cols = ((v.n + kEX * vx - 1) / (kEX * vx)) * ((v.n + kEY - 1) / kEY);
-    int ntz = kDiagTiles / cols;
-    ntz = ntz < 1 ? 1 : (ntz > v.n ? v.n : ntz);
-    const int tz = (v.n + ntz - 1) / ntz;
-    nb = cols * ((v.n + tz - 1) / tz);
-    if (vx == 2) {
-      if constexpr (sizeof(T) == 8 && NF <= 2)
-        hipLaunchKernelGGL((energies7_kernel<T, NF, KIND, 2>), dim3(nb), dim3(kBlock), 0, s, B, v.sc,
-                           v.prm, v.n, v.zs, tz, v.partials);
-    } else {
-      hipLaunchKernelGGL((energies7_kernel<T, NF, KIND, 1>), dim3(nb), dim3(kBlock), 0, s, B, v.sc,
-                         v.prm, v.n, v.zs, tz, v.partials);
+  // z-chunks so that the tiles number about kDiagTiles (at most one chunk
+  // per plane).  Two sites per lane in FP64 where rows divide, with up to
+  // two fields (registers): 157 us a call at 256^3 with two fields against
+  // 172; in FP32, where a lane's load stays short of 16 bytes, one site is
+  // as fast or faster (111 against 114 us there, 835 against 874 at 512^3
+  // q-ball)
+  const int vx = v.st.kind == 0 && sizeof(T) == 8 && NF <= 2 && v.n % 2 == 0 ? 2 : 1;
+  const int cols = ((v.n + kEX * vx - 1) / (kEX * vx)) * ((v.n + kEY - 1) / kEY);
+  int ntz = kDiagTiles / cols;
+  ntz = ntz < 1 ? 1 : (ntz > v.n ? v.n : ntz);
+  const int tz = (v.n + ntz - 1) / ntz, nb = cols * ((v.n + tz - 1) / tz);
+  if (v.st.kind != 0) {
+    const size_t lds = size_t(3) * NF * (kEX + 2) * (kEY + 2) * sizeof(double);
+    if (lds > 65536) {  // above 64 KB a kernel has to be told
+      const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(energies27_kernel<T, NF, KIND>),
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
+      if (e != hipSuccess) return e;
     }
+    hipLaunchKernelGGL((energies27_kernel<T, NF, KIND>), dim3(nb), dim3(kBlock), lds, s, B, v.sc,
+                       v.prm, v.n, v.zs, tz, v.st, v.partials);
+  } else if (vx == 2) {
+    if constexpr (sizeof(T) == 8 && NF <= 2)
+      hipLaunchKernelGGL((energies7_kernel<T, NF, KIND, 2>), dim3(nb), dim3(kBlock), 0, s, B, v.sc,
+                         v.prm, v.n, v.zs, tz, v.partials);
   } else {
-    nb = int((n3 + kBlock - 1) / kBlock);
-    if (nb > kDiagBlocksMax) nb = kDiagBlocksMax;
-    hipLaunchKernelGGL((energies_kernel<T, NF, KIND>), dim3(nb), dim3(kBlock), 0, s, B, v.sc,
-                       v.prm, v.n, v.zs, v.st, v.partials);
+    hipLaunchKernelGGL((energies7_kernel<T, NF, KIND, 1>), dim3(nb), dim3(kBlock), 0, s, B, v.sc,
+                       v.prm, v.n, v.zs, tz, v.partials);
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
