@@ -12,21 +12,18 @@ namespace symlat {
 // Where a handle's small results land.  A copy into the caller's pageable
 // memory took 11.4 us more than the kernel before it and the wait, one into
 // pinned memory 3 us: one step of a 32^3 lattice and a look at its background
-// 43.4 -> 35.7 us, a read-out of its energies (two copies before, one now)
-// 46.8 -> 28.3.  Where no pinned memory is to be had, ordinary memory.
+// 43.4 -> 35.7 us.  A kernel that ends a call's work stores its results there
+// itself: a read-out of the energies, with two copies 46.8 us, with one kernel
+// that gathered them 28.1, now takes 26.3.  Where no pinned memory is to
+// be had, ordinary memory.
 class ReadBack {
  public:
   ~ReadBack();
   void reserve(size_t bytes);
   // One copy, then a wait for the stream; the result stays until the next.
   hipError_t one(const void* src, size_t bytes, hipStream_t s, const unsigned char** out);
-  // Up to three pieces of whole 8-byte words, one behind the other, stored by
-  // a kernel on the current device, then a wait for the stream.
-  struct Piece {
-    const void* src;
-    size_t bytes;
-  };
-  hipError_t several(const Piece* p, int np, hipStream_t s, const unsigned char** out);
+  // Where a kernel may store `bytes` for the host; NULL without pinned memory.
+  unsigned char* direct(size_t bytes) { return bytes <= cap_ ? pin_ : nullptr; }
 
  private:
   unsigned char* room(size_t bytes);

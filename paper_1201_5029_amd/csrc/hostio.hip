@@ -10,22 +10,6 @@
 
 namespace symlat {
 
-namespace {
-
-struct Pieces {
-  const unsigned long long* src[3];
-  unsigned words[3];
-};
-
-__global__ __launch_bounds__(256) void read_back_kernel(Pieces p, unsigned long long* out) {
-  for (int k = 0; k < 3; ++k) {
-    for (unsigned i = threadIdx.x; i < p.words[k]; i += 256) out[i] = p.src[k][i];
-    out += p.words[k];
-  }
-}
-
-}  // namespace
-
 ReadBack::~ReadBack() {
   if (pin_) (void)hipHostFree(pin_);
 }
@@ -54,28 +38,6 @@ hipError_t ReadBack::one(const void* src, size_t bytes, hipStream_t s, const uns
   *out = dst;
   if (!dst) return hipErrorOutOfMemory;
   const hipError_t e = hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, s);
-  return e == hipSuccess ? hipStreamSynchronize(s) : e;
-}
-
-hipError_t ReadBack::several(const Piece* p, int np, hipStream_t s, const unsigned char** out) {
-  size_t bytes = 0;
-  Pieces P{};
-  for (int k = 0; k < np; ++k) {
-    P.src[k] = static_cast<const unsigned long long*>(p[k].src);
-    P.words[k] = unsigned(p[k].bytes / 8);
-    bytes += p[k].bytes;
-  }
-  unsigned char* dst = room(bytes);
-  *out = dst;
-  if (!dst) return hipErrorOutOfMemory;
-  hipError_t e = hipSuccess;
-  if (dst == pin_) {
-    hipLaunchKernelGGL(read_back_kernel, dim3(1), dim3(256), 0, s, P, reinterpret_cast<unsigned long long*>(dst));
-    e = hipGetLastError();
-  } else {
-    for (int k = 0; k < np && e == hipSuccess; dst += p[k].bytes, ++k)
-      e = hipMemcpyAsync(dst, p[k].src, p[k].bytes, hipMemcpyDeviceToHost, s);
-  }
   return e == hipSuccess ? hipStreamSynchronize(s) : e;
 }
 

@@ -351,7 +351,8 @@ hipError_t launch_spectrum_bins(const LatView& v, const FftPlan& P, const ModeBu
 hipError_t launch_mode_bins(const LatView& v, int momentum, const FftPlan& P, const ModeBuf& B,
                             const double2* tw, const double* ax, int nbe, int rows, const double* m2_dev,
                             hipStream_t s);
-hipError_t launch_mode_bins_finalize(const LatView& v, const ModeBuf& B, int nbe, int rows, double* out5,
+hipError_t launch_mode_bins_finalize(const LatView& v, const ModeBuf& B, int nbe, int rows,
+                                     const double* m2_dev, double* out5,
                                      hipStream_t s);
 
 }  // namespace symlat

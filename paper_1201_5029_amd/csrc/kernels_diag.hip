@@ -443,7 +443,8 @@ __global__ __launch_bounds__(kBlock) void energies27_kernel(Bufs B, const DevSca
 }
 
 // Reduce energies partials, compute observables; mode 1 also solves the
-// constraint H = 0 for p_a (expanding branch) and sets S2.
+// constraint H = 0 for p_a (expanding branch) and sets S2.  In mode 0 the
+// scalars follow the observables, so that one place holds what a call returns.
 template <int NF>
 __global__ __launch_bounds__(kBlock) void energies_finalize(const double* partials, int nblocks,
                                                            DevScalars* sc, BgConsts K, int n,
@@ -489,6 +490,11 @@ __global__ __launch_bounds__(kBlock) void energies_finalize(const double* partia
     sums_out[threadIdx.x] = s[threadIdx.x];
   }
   __syncthreads();
+  // the scalars behind a read-out (mode 0 leaves them as they are)
+  constexpr int kWords = int(sizeof(DevScalars) / sizeof(uint64_t));
+  static_assert(kWords <= 64 && sizeof(sl_energies_t) % sizeof(uint64_t) == 0, "whole words");
+  if (mode == 0 && threadIdx.x >= 64 && threadIdx.x < 64 + kWords)
+    reinterpret_cast<uint64_t*>(out + 1)[threadIdx.x - 64] = reinterpret_cast<const uint64_t*>(sc)[threadIdx.x - 64];
   if (threadIdx.x != 0) return;
   const double VL = K.VL;
   const double a = S.a;

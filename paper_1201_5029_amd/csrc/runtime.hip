@@ -352,8 +352,8 @@ struct AuxLayout {
     partials1 = take(size_t(kChainMaxTiles) * 6 * sizeof(double));
     sink = take(kSinkBytes);
     sums = take(sizeof(double) * (5 * kMaxFields + 1));
-    energies = take(sizeof(sl_energies_t));
-    spec = take(sizeof(double) * 3 * kMaxBins);
+    energies = take(sizeof(sl_energies_t) + sizeof(DevScalars));
+    spec = take(sizeof(double) * 3 * kMaxBins);  // 5 values per bin that a mode reaches, m_eff^2, scalars
     total = o;
   }
 };
@@ -489,12 +489,23 @@ sl_status read_scalars(sl_lattice* L, DevScalars* S) {
   return apply_scalars(L, *S);
 }
 
-// The scalars behind other results, in one read-back: *h is where the pieces
-// begin.
-sl_status read_with_scalars(sl_lattice* L, ReadBack::Piece first, ReadBack::Piece second,
-                            const char* what, const unsigned char** h) {
-  const ReadBack::Piece p[3] = {first, second, {L->v.sc, sizeof(DevScalars)}};
-  const hipError_t e = L->back.several(p, 3, L->stream, h);
+// Results that the last kernel of a call stores, with the scalars behind them:
+// where it shall (the handle's pinned memory, else `dev`) ...
+void* result_place(sl_lattice* L, void* dev, size_t bytes) {
+  void* p = L->back.direct(bytes);
+  return p ? p : dev;
+}
+
+// ... and, once it is enqueued, where they are on the host.
+sl_status result_wait(sl_lattice* L, const void* place, const void* dev, size_t bytes, const char* what,
+                      const unsigned char** h) {
+  hipError_t e;
+  if (place != dev) {
+    *h = static_cast<const unsigned char*>(place);
+    e = hipStreamSynchronize(L->stream);
+  } else {
+    e = L->back.one(dev, bytes, L->stream, h);
+  }
   if (e != hipSuccess) return fail(SL_E_DEVICE, "%s: %s", what, hipGetErrorString(e));
   return SL_OK;
 }
@@ -673,14 +684,15 @@ hipError_t transform_rows(sl_lattice* L, int field, int momentum, const SpecScra
 // Field power spectrum in the scratch S; synchronises the lattice's stream.
 sl_status spectrum_run(sl_lattice* L, int field, int nbins, const SpecScratch& S, double* k_out,
                        double* p_out, int64_t* count_out) {
+  const size_t count = size_t(3) * S.nbe, bytes = count * sizeof(double) + sizeof(DevScalars);
+  double* place = static_cast<double*>(result_place(L, L->spec_dev, bytes));
   hipError_t e = launch_fft_tables(L->cfg.n, L->v.st, S.tw, S.ax, L->stream);
   if (e == hipSuccess) e = transform_rows(L, field, 0, S);
   if (e == hipSuccess)
-    e = launch_spectrum_bins(L->v, S.P, S.B, S.tw, S.ax, S.nbe, S.rows, L->spec_dev, L->stream);
+    e = launch_spectrum_bins(L->v, S.P, S.B, S.tw, S.ax, S.nbe, S.rows, place, L->stream);
   if (e != hipSuccess) return fail(SL_E_DEVICE, "spectrum: %s", hipGetErrorString(e));
-  const size_t count = size_t(3) * S.nbe;
   const unsigned char* h = nullptr;
-  const sl_status st = read_with_scalars(L, {L->spec_dev, count * sizeof(double)}, {}, "spectrum", &h);
+  const sl_status st = result_wait(L, place, L->spec_dev, bytes, "spectrum", &h);
   if (st != SL_OK) return st;
   const double* host = reinterpret_cast<const double*>(h);
   for (int k = 0; k < nbins; ++k) {
@@ -1302,9 +1314,11 @@ sl_status sl_energies(sl_lattice* L, sl_energies_t* out) {
   sl_status st = require_state(L);
   if (st != SL_OK) return st;
   if (!out) return fail(SL_E_INVALID, "out is NULL");
-  HIP_TRY(launch_energies(L->v, L->sums_dev, L->energies_dev, 0, L->stream));
+  const size_t bytes = sizeof(sl_energies_t) + sizeof(DevScalars);
+  void* place = result_place(L, L->energies_dev, bytes);
+  HIP_TRY(launch_energies(L->v, L->sums_dev, static_cast<sl_energies_t*>(place), 0, L->stream));
   const unsigned char* h = nullptr;
-  st = read_with_scalars(L, {L->energies_dev, sizeof(sl_energies_t)}, {}, "energies", &h);
+  st = result_wait(L, place, L->energies_dev, bytes, "energies", &h);
   if (st != SL_OK) return st;
   std::memcpy(out, h, sizeof(sl_energies_t));
   return scalars_behind(L, h + sizeof(sl_energies_t));
@@ -1378,11 +1392,12 @@ sl_status sl_spectra(sl_lattice* L, int32_t field, int32_t nbins, double* k_out,
     if (e == hipSuccess)
       e = launch_mode_bins(L->v, momentum, S.P, S.B, S.tw, S.ax, S.nbe, S.rows, S.m2, L->stream);
   }
-  if (e == hipSuccess) e = launch_mode_bins_finalize(L->v, S.B, S.nbe, S.rows, L->spec_dev, L->stream);
+  const size_t count = size_t(5) * S.nbe, bytes = (count + 1) * sizeof(double) + sizeof(DevScalars);
+  double* place = static_cast<double*>(result_place(L, L->spec_dev, bytes));
+  if (e == hipSuccess) e = launch_mode_bins_finalize(L->v, S.B, S.nbe, S.rows, S.m2, place, L->stream);
   if (e != hipSuccess) return fail(SL_E_DEVICE, "spectra: %s", hipGetErrorString(e));
-  const size_t count = size_t(5) * S.nbe;
   const unsigned char* h = nullptr;
-  st = read_with_scalars(L, {L->spec_dev, count * sizeof(double)}, {S.m2, sizeof(double)}, "spectra", &h);
+  st = result_wait(L, place, L->spec_dev, bytes, "spectra", &h);
   if (st != SL_OK) return st;
   const double* host = reinterpret_cast<const double*>(h);
   for (int b = 0; b < nbins; ++b) {

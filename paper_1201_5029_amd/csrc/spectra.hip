@@ -257,12 +257,13 @@ __global__ __launch_bounds__(NT, NT == 512 ? 4 : 3) void bin_columns_kernel(FftP
 // through the rows of each (17 us for 768 rows of 5 + 2 sums, 222 bins; 38 us
 // with 16 bins to a workgroup, where 14 CUs worked; one thread per bin took 100
 // us for 256 rows of 5); out =
-// [k | <|F|^2> (| <rho> | <n>) | count], nbe values each.  rows2 > 0: rows of
-// the momentum's part follow.
+// [k | <|F|^2> (| <rho> | <n>) | count], nbe values each, then m_eff^2 (NV = 5)
+// and the scalars.  rows2 > 0: rows of the momentum's part follow.
 constexpr int kFinBins = 4;
 template <int NV>
 __global__ __launch_bounds__(1024) void bin_finalize_kernel(ModeBuf B, int rows, int rows2, int nbe,
-                                                            double L, double* out) {
+                                                            double L, const DevScalars* sc,
+                                                            const double* m2, double* out) {
   __shared__ KSum sh[NV][16][kFinBins];
   constexpr int G = 1024 / kFinBins;
   const int t = int(threadIdx.x), i = t % kFinBins, g = t / kFinBins, wave = t >> 6;
@@ -270,6 +271,13 @@ __global__ __launch_bounds__(1024) void bin_finalize_kernel(ModeBuf B, int rows,
   const bool own = b < nbe;
   const double* p1 = B.part[B.sc ? B.sc->parity ^ 1 : 0] + b;
   const double* p2 = p1 + size_t(rows) * NV * nbe;
+  if (blockIdx.x == 0) {
+    double* tail = out + size_t(NV) * nbe;
+    if (NV == 5 && t == 64) tail[0] = *m2;
+    const int w = t - 128;
+    if (w >= 0 && w < int(sizeof(DevScalars) / sizeof(uint64_t)))
+      reinterpret_cast<uint64_t*>(tail + (NV == 5 ? 1 : 0))[w] = reinterpret_cast<const uint64_t*>(sc)[w];
+  }
   KSum v[NV];
 #pragma unroll
   for (int q = 0; q < NV; ++q) v[q] = KSum{0.0, 0.0};
@@ -397,7 +405,7 @@ hipError_t launch_spectrum_bins(const LatView& v, const FftPlan& P, const ModeBu
   const hipError_t e = bin_columns<kBinField>(P, B, tw, ax, rows, bin_args(v, nbe, nullptr), s);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(bin_finalize_kernel<3>, dim3((nbe + kFinBins - 1) / kFinBins), dim3(1024), 0, s, B, rows, 0, nbe, v.bg.L,
-                     out3);
+                     v.sc, static_cast<const double*>(nullptr), out3);
   return hipGetLastError();
 }
 
@@ -410,10 +418,11 @@ hipError_t launch_mode_bins(const LatView& v, int momentum, const FftPlan& P, co
   return bin_columns<kBinSpectraMomentum>(P, after, tw, ax, rows, bin_args(v, nbe, m2_dev), s);
 }
 
-hipError_t launch_mode_bins_finalize(const LatView& v, const ModeBuf& B, int nbe, int rows, double* out5,
+hipError_t launch_mode_bins_finalize(const LatView& v, const ModeBuf& B, int nbe, int rows,
+                                     const double* m2_dev, double* out5,
                                      hipStream_t s) {
   hipLaunchKernelGGL(bin_finalize_kernel<5>, dim3((nbe + kFinBins - 1) / kFinBins), dim3(1024), 0, s, B, rows, rows, nbe, v.bg.L,
-                     out5);
+                     v.sc, m2_dev, out5);
   return hipGetLastError();
 }
 
