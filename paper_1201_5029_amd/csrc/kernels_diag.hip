@@ -50,8 +50,8 @@ constexpr int nsums() { return 5 * NF + 1; }
 // times a rounding error, is not summed).  The kernel is bound by
 // instructions: with all six neighbours and D a read-out took 196 us at 256^3
 // in FP64 with two fields and 143 us in FP32, whatever the loads' distance; now
-// 140 and 94 us (about 25 us of each is the launches and the copy back; before,
-// 40), and 1025 -> 823 us at 512^3 q-ball.
+// 138 and 92 us (about 23 us of each is the launches and the wait; before, 40),
+// and 1025 -> 803 us at 512^3 q-ball.
 // The loads run two planes ahead of the arithmetic, in two register sets used
 // in turn.  A lane adds its sites' terms plainly over the chunk and the lanes'
 // and tiles' totals are combined with compensation.
