@@ -559,9 +559,9 @@ hipError_t energies_t(const LatView& v, double* sums, sl_energies_t* out, int mo
   // z-chunks so that the tiles number about kDiagTiles (at most one chunk
   // per plane).  Two sites per lane in FP64 where rows divide, with up to
   // two fields (registers): 157 us a call at 256^3 with two fields against
-  // 172; in FP32, where a lane's load stays short of 16 bytes, one site is
-  // as fast or faster (111 against 114 us there, 835 against 874 at 512^3
-  // q-ball)
+  // 172 (both with the former read-back, some 17 us more); in FP32, where a
+  // lane's load stays short of 16 bytes, one site is as fast or faster (111
+  // against 114 us there, 835 against 874 at 512^3 q-ball)
   const int vx = v.st.kind == 0 && sizeof(T) == 8 && NF <= 2 && v.n % 2 == 0 ? 2 : 1;
   const int cols = ((v.n + kEX * vx - 1) / (kEX * vx)) * ((v.n + kEY - 1) / kEY);
   int ntz = kDiagTiles / cols;
