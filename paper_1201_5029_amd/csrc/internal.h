@@ -131,6 +131,9 @@ inline bool pf_valid(int pf) {
   return pf >= 1 && pf <= 7 && pf_depth(pf) != 0 && (pf_depth(pf) != 3 || pf_nt(pf));
 }
 
+// Tiles of a pass at most: the partial-sum buffer holds a record for each.
+constexpr long kMaxPassBlocks = 65536;
+
 struct Tile {
   int tx, ty, tz, vx;
   int pf;  // pass mode: prefetch depth (1, 2 or 3) | kPfNontemporal

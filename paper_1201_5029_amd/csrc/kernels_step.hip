@@ -1256,6 +1256,7 @@ hipError_t launch_pass(const LatView& v, const Chain& c, hipStream_t s) {
   if (pf_nt(v.tile.pf) && v.tile.vx < 2) return hipErrorInvalidValue;
   // the 27-point pass needs lanes for 2 rows + 2 columns + 4 corners of halo
   if (v.st.kind != 0 && 2 * v.tile.tx + 2 * v.tile.ty + 4 > kBlock) return hipErrorInvalidValue;
+  if (v.tile.nblocks() > kMaxPassBlocks) return hipErrorInvalidValue;
   if (c.chain && v.tile.nblocks() > kChainMaxTiles) return hipErrorInvalidValue;
   const PassKernel k = pick(v.prec, v.pot, v.nf, v.tile, v.st.kind);
   hipLaunchKernelGGL(k.fn, dim3(v.tile.nblocks()), dim3(kBlock), k.lds, s, make_params(v), c);

@@ -143,7 +143,6 @@ bool config_ok(const sl_config* c, std::string* why) {
 
 namespace {
 
-constexpr long kMaxPassBlocks = 65536;  // bound of the per-block partial-sum buffer
 constexpr int64_t kEvolveChunk = 32;     // steps per captured evolve graph
 constexpr int64_t kBatchChunk = 8;       // steps per captured batch graph
 
@@ -537,6 +536,18 @@ void retile_default(sl_lattice* L) {
   retile(L, 0, vx, 0, pf);
   L->tz_user = 0;
   L->shape_default = true;
+}
+
+// The current shape with z-chunks of tz planes instead of its own (tz > 0),
+// where that many tiles have records: fewer sites per lane than the shape the
+// length was accepted with make more tiles.
+void keep_chunk(sl_lattice* L, int tz) {
+  const Tile& c = L->v.tile;
+  if (tz <= 0) return;
+  const Tile t = tile_geometry(L->cfg.n, c.tx, c.vx, tz, c.pf);
+  if (long(t.nblocks()) > kMaxPassBlocks) return;
+  L->v.tile = t;
+  L->tz_user = tz;
 }
 
 void refresh_m2max(sl_lattice* L) {
@@ -1737,10 +1748,7 @@ sl_status sl_set_stencil(sl_lattice* L, const double* c) {
     } else {
       const int tz = L->tz_user;
       retile_default(L);
-      if (tz > 0) {  // a chunk length given by hand stays
-        L->tz_user = tz;
-        retile(L, L->v.tile.tx, L->v.tile.vx, tz, L->v.tile.pf);
-      }
+      keep_chunk(L, tz);
     }
   }
   if (L->batch) batch_member_changed(L->batch);
@@ -1857,6 +1865,8 @@ sl_status batch_upload(sl_batch* B) {
     br[r].offs[1] = L->v.offs1;
     br[r].bg = L->v.bg;
     br[r].ntiles = L->v.tile.nblocks();
+    if (br[r].ntiles > kMaxPassBlocks)
+      return fail(SL_E_INVALID, "a member's tile gives %d workgroups (limit %ld)", br[r].ntiles, kMaxPassBlocks);
     br[r].pad = 0;
     start[r + 1] = start[r] + br[r].ntiles;
     const size_t l = pass_lds_bytes(B->prec, B->nf, L->v.tile);

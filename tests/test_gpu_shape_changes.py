@@ -1,0 +1,43 @@
+"""The pass shape after a change of the stencil kind: it is chosen anew for the
+new kernel, and a z-chunk length given by hand stays only where its tiles number
+no more than the partial-sum buffer has records for."""
+import math
+
+import pytest
+
+import paper_1201_5029_amd as sl
+from gpu_util import say
+
+pytestmark = pytest.mark.gpu
+
+MOST_TILES = 65536
+
+
+@pytest.fixture(autouse=True)
+def _forget_tuned_shapes():
+    sl.symlat.autotune_forget()
+    yield
+    sl.symlat.autotune_forget()
+
+
+def _tiles(n, shape):
+    tx, vx, ty, tz, _ = shape
+    return math.ceil(n / (tx * vx)) * math.ceil(n / ty) * math.ceil(n / tz)
+
+
+@pytest.mark.parametrize("tz", [2, 3, 16])
+def test_given_chunk_within_the_tile_limit(tz):
+    """512^3, two FP32 fields: four sites per lane and two planes a chunk make
+    exactly 65536 tiles, the 27-point pass's two sites per lane twice as many.
+    No pass is launched."""
+    n = 512
+    lat = sl.Lattice(n, 2, 40.0, precision="f32")
+    lat.set_potential("chaotic2", (1.0, 100.0))
+    lat.set_tile(64, 4, tz, 7)
+    assert _tiles(n, lat.tile()) <= MOST_TILES
+    lat.set_stencil("27")
+    say("tz", tz, "27-point shape", lat.tile(), "tiles", _tiles(n, lat.tile()))
+    assert _tiles(n, lat.tile()) <= MOST_TILES
+    if tz == 16:                                  # few enough: the length stays
+        assert lat.tile()[3] == 16
+    lat.close()
