@@ -176,7 +176,10 @@ sl_status sl_set_potential(sl_lattice* lat, int32_t kind, const double* params, 
  * (vx = 1 or 2 sites per lane, pf = 1, or pf = 5 with vx = 2).  The stencil enters the kick, the
  * p_a sums, the observables, the stability bound (largest k_eff^2 over the
  * zone) and the vacuum mode frequencies, so set it before
- * sl_init_fluctuations.  c is a host array of 4 doubles.  SL_E_INVALID for
+ * sl_init_fluctuations.  A change between the 7-point and another member
+ * chooses the pass shape anew, except that a z-chunk length of sl_set_tile
+ * stays where its tiles are within that call's limit.  c is a host array of
+ * 4 doubles.  SL_E_INVALID for
  * non-finite values or a member outside the family (tolerance 1e-12 of the
  * weighted coefficient sum); SL_E_STATE for a change of stencil kind while
  * the lattice belongs to a batch.  sl_get_stencil copies the weights out. */

@@ -449,6 +449,7 @@ struct sl_lattice {
   int chain_mode = -1;  // sl_set_chaining
   sl_batch* batch = nullptr;  // batch this lattice belongs to, if any
   int tz_user = 0;            // 0: z-chunk chosen by best_tile
+  bool tz_given = false;      // tz_user from sl_set_tile (else from a tuner or a batch)
   bool shape_default = true;  // shape from retile_default
   std::vector<std::pair<hipEvent_t, hipEvent_t>> events;
   // captured interior chunk of evolve (kEvolveChunk steps, every finalize
@@ -535,19 +536,27 @@ void retile_default(sl_lattice* L) {
   lane_shape(L->cfg.n, L->cfg.precision, L->cfg.nfields, L->v.st.kind, &vx, &pf);
   retile(L, 0, vx, 0, pf);
   L->tz_user = 0;
+  L->tz_given = false;
   L->shape_default = true;
 }
 
-// The current shape with z-chunks of tz planes instead of its own (tz > 0),
-// where that many tiles have records: fewer sites per lane than the shape the
+// A shape that a tuner or a batch brings.
+void retile_tuned(sl_lattice* L, int tx, int vx, int tz, int pf) {
+  retile(L, tx, vx, tz, pf);
+  L->tz_user = tz;
+  L->tz_given = false;
+  L->shape_default = false;
+}
+
+// The current shape with z-chunks of tz planes, a length given by hand, where that many tiles have records: fewer sites per lane than the shape the
 // length was accepted with make more tiles.
 void keep_chunk(sl_lattice* L, int tz) {
   const Tile& c = L->v.tile;
-  if (tz <= 0) return;
   const Tile t = tile_geometry(L->cfg.n, c.tx, c.vx, tz, c.pf);
   if (long(t.nblocks()) > kMaxPassBlocks) return;
   L->v.tile = t;
   L->tz_user = tz;
+  L->tz_given = true;
 }
 
 void refresh_m2max(sl_lattice* L) {
@@ -1011,9 +1020,7 @@ sl_status sl_set_potential(sl_lattice* L, int32_t kind, const double* params, in
   const TuneKey key{L->device, L->cfg.n, L->cfg.nfields, L->cfg.precision, kind, L->v.st.kind};
   TuneVal tv;
   if (tune_cache().find(key, &tv)) {
-    L->tz_user = tv.tz;
-    retile(L, tv.tx, tv.vx, tv.tz, tv.pf);
-    L->shape_default = false;
+    retile_tuned(L, tv.tx, tv.vx, tv.tz, tv.pf);
   }
   return SL_OK;
 }
@@ -1653,9 +1660,7 @@ sl_status sl_autotune(sl_lattice* L, int32_t reps, int32_t vx_only, int32_t pf_o
     L->tz_user = saved_tz;
     return fail(SL_E_DEVICE, "autotune: %s", hipGetErrorString(err));
   }
-  L->tz_user = win.tz;
-  retile(L, win.tx, win.vx, win.tz, win.pf);
-  L->shape_default = false;
+  retile_tuned(L, win.tx, win.vx, win.tz, win.pf);
   const TuneKey key{L->device, n, L->cfg.nfields, L->cfg.precision, L->v.pot, L->v.st.kind};
   tune_cache().put(key, {win.tx, win.vx, win.tz, win.pf});
   if (L->batch) batch_member_changed(L->batch);
@@ -1703,6 +1708,7 @@ sl_status sl_set_tile(sl_lattice* L, int32_t tx, int32_t vx, int32_t tz, int32_t
     return fail(SL_E_INVALID, "tile gives %d workgroups (limit %ld)", t.nblocks(), kMaxPassBlocks);
   HIP_TRY(hipStreamSynchronize(L->stream));
   L->tz_user = tz;
+  L->tz_given = tz > 0;
   retile(L, tx, vx, tz, pf);
   L->shape_default = false;
   if (L->batch) batch_member_changed(L->batch);
@@ -1742,13 +1748,11 @@ sl_status sl_set_stencil(sl_lattice* L, const double* c) {
     const TuneKey key{L->device, L->cfg.n, L->cfg.nfields, L->cfg.precision, L->v.pot, kind};
     TuneVal tv;
     if (L->pot_set && tune_cache().find(key, &tv)) {
-      L->tz_user = tv.tz;
-      retile(L, tv.tx, tv.vx, tv.tz, tv.pf);
-      L->shape_default = false;
+      retile_tuned(L, tv.tx, tv.vx, tv.tz, tv.pf);
     } else {
-      const int tz = L->tz_user;
+      const int given = L->tz_given ? L->tz_user : 0;
       retile_default(L);
-      keep_chunk(L, tz);
+      if (given > 0) keep_chunk(L, given);
     }
   }
   if (L->batch) batch_member_changed(L->batch);
@@ -1988,9 +1992,7 @@ sl_status sl_batch_add(sl_batch* B, sl_lattice* L) {
   }
   if (tx != L->v.tile.tx || vx != L->v.tile.vx || pf != L->v.tile.pf || tz != L->tz_user) {
     HIP_TRY(hipStreamSynchronize(L->stream));
-    L->tz_user = tz;
-    retile(L, tx, vx, tz, pf);
-    L->shape_default = false;
+    retile_tuned(L, tx, vx, tz, pf);
   }
   if (B->runs.empty()) {
     B->prec = L->cfg.precision;
@@ -2105,9 +2107,7 @@ sl_status sl_batch_autotune(sl_batch* B, int32_t reps, double* best_ms) {
   auto apply = [&](int n, int tx, int vx, int tz, int pf) {
     for (sl_lattice* L : B->runs)
       if (L->cfg.n == n) {
-        L->tz_user = tz;
-        retile(L, tx, vx, tz, pf);
-        L->shape_default = false;
+        retile_tuned(L, tx, vx, tz, pf);
       }
     B->shape.vx = vx;
     B->shape.pf = pf;

@@ -41,3 +41,28 @@ def test_given_chunk_within_the_tile_limit(tz):
     if tz == 16:                                  # few enough: the length stays
         assert lat.tile()[3] == 16
     lat.close()
+
+
+def test_tuned_chunk_is_not_a_given_one():
+    """What a tuner found for the 7-point pass (the batch tuner's chunks have at
+    least four planes) says nothing of the 27-point one: after the change the
+    shape is that of a lattice never tuned, at 48^3 one plane a chunk."""
+    def fresh():
+        lat = sl.Lattice(48, 2, 20.0, precision="f32")
+        lat.set_potential("chaotic2", (1.0, 10.0))
+        return lat
+    want = fresh()
+    want.set_stencil("27")
+    lat = fresh()
+    lat.init_fluctuations((0.5, 0.0), (0.0, 0.0), "white", 1e-3, 3)
+    b = sl.Batch()
+    b.add(lat)
+    b.autotune(reps=1)
+    tuned = lat.tile()
+    b.remove(lat)
+    b.close()
+    lat.set_stencil("27")
+    say("tuned", tuned, "27-point", lat.tile(), "never tuned", want.tile())
+    assert tuned[3] >= 4 and lat.tile() == want.tile()
+    lat.close()
+    want.close()
