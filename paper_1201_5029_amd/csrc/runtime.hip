@@ -1966,6 +1966,7 @@ sl_status sl_batch_add(sl_batch* B, sl_lattice* L) {
   // a size the batch tuner has seen starts with its tuned shape; a member
   // takes the batch's per-lane shape (vx, pf)
   int tx = L->v.tile.tx, vx = L->v.tile.vx, tz = L->tz_user, pf = L->v.tile.pf;
+  int given = 0;  // a chunk length given by hand to a shape that changes here
   const BatchTuneKey key{{L->device, L->cfg.n, L->cfg.nfields, L->cfg.precision, L->v.pot, L->v.st.kind},
                          0, 0};
   TuneVal tv;
@@ -1981,6 +1982,7 @@ sl_status sl_batch_add(sl_batch* B, sl_lattice* L) {
       vx = bvx;
       pf = bpf;
       tx = tz = 0;
+      given = L->tz_given ? L->tz_user : 0;
     }
   }
   if (!B->runs.empty() && (vx != B->shape.vx || pf != B->shape.pf)) {
@@ -1993,6 +1995,7 @@ sl_status sl_batch_add(sl_batch* B, sl_lattice* L) {
   if (tx != L->v.tile.tx || vx != L->v.tile.vx || pf != L->v.tile.pf || tz != L->tz_user) {
     HIP_TRY(hipStreamSynchronize(L->stream));
     retile_tuned(L, tx, vx, tz, pf);
+    if (given > 0) keep_chunk(L, given);
   }
   if (B->runs.empty()) {
     B->prec = L->cfg.precision;

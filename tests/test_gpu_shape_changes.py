@@ -66,3 +66,28 @@ def test_tuned_chunk_is_not_a_given_one():
     assert tuned[3] >= 4 and lat.tile() == want.tile()
     lat.close()
     want.close()
+
+
+def test_first_batch_member_keeps_its_given_chunk():
+    """128^3, one FP32 field: the shape of the 7-point pass is the default (four
+    sites per lane) but for its chunk length; the first member brings two sites
+    per lane into a batch, which more sides can share, and the same chunk."""
+    lat = sl.Lattice(128, 1, 20.0, precision="f32")
+    lat.set_potential("free", (1.0,))
+    lat.set_stencil("27")
+    lat.set_tile(16, 1, 12, 1)
+    lat.set_stencil("7")
+    assert lat.tile()[1] == 4 and lat.tile()[3] == 12
+    lat.init_fluctuations((0.5,), (0.0,), "white", 1e-3, 3)
+    other = sl.Lattice(66, 1, 20.0, precision="f32")
+    other.set_potential("free", (1.0,))
+    other.init_fluctuations((0.5,), (0.0,), "white", 1e-3, 4)
+    b = sl.Batch()
+    b.add(lat)
+    b.add(other)
+    say("member", lat.tile(), "second", other.tile())
+    assert lat.tile()[1] == 2 and lat.tile()[3] == 12 and other.tile()[1] == 2
+    b.step(2, 0.005, 4)
+    b.close()
+    lat.close()
+    other.close()
