@@ -275,10 +275,12 @@ __global__ __launch_bounds__(kBlock) void energies7_kernel(Bufs B, const DevScal
 // and three planes are kept (one barrier per plane).  With
 // G = 1/2 sum_d c_d (f(x + d) - f(x))^2 and D f = sum_d c_d (f(x + d) - f(x))
 // + rest f, rest = c0 + 6 c1 + 12 c2 + 8 c3 (0 up to rounding),
-// sum_x f D f = -sum_x G + rest sum_x f^2.  It is bound by instructions and
-// LDS reads: a read-out takes 196 us at 256^3 in FP64 with two fields and 140 in
-// FP32 (206 and 156 with 1024 tiles instead of 512); with each site reading 26
-// neighbours and their momenta from memory it took 1054 and 575 us.
+// sum_x f D f = -sum_x G + rest sum_x f^2.  Every term is added with
+// compensation: 128 planes of a homogeneous state added plainly were 3.4e-15 of
+// the total off, now less than 3e-16.  It is bound by instructions and LDS reads:
+// a read-out takes 188 us at 256^3 in FP64 with two fields and 156 in FP32 (184
+// and 135 with plain sums); with each site reading 26 neighbours and their
+// momenta from memory it took 1053 and 591 us.
 template <typename T, int NF, int KIND>
 __global__ __launch_bounds__(kBlock) void energies27_kernel(Bufs B, const DevScalars* sc,
                                                            PotArgs prm, int n, int zs, int tz,
@@ -352,9 +354,9 @@ __global__ __launch_bounds__(kBlock) void energies27_kernel(Bufs B, const DevSca
   }
 
   auto wrapz = [n](int zz) { return zz >= n ? zz - n : zz; };
-  double part[NV];
+  KSum acc[NV];
 #pragma unroll
-  for (int k = 0; k < NV; ++k) part[k] = 0.0;
+  for (int k = 0; k < NV; ++k) acc[k] = KSum{0.0, 0.0};
   double fc[NF], pc[NF], fn[NF], pn[NF];  // own site at z and z + 1
   T lf[NF], lp[NF], hf[NF], hp[NF];       // loads in flight: own site, halo cell
   auto issue = [&](int zz) {
@@ -409,15 +411,15 @@ __global__ __launch_bounds__(kBlock) void energies27_kernel(Bufs B, const DevSca
         const double faces = sq(fn[i], sq(A[LX], sq(A[1], 0.0)));
         const double edges = sq(U[LX], sq(U[-LX], sq(U[1], sq(U[-1], sq(A[LX + 1], sq(A[LX - 1], 0.0))))));
         const double corners = sq(U[LX + 1], sq(U[LX - 1], sq(U[-LX + 1], sq(U[-LX - 1], 0.0))));
-        part[5 * i + 0] = fma(pc[i], pc[i], part[5 * i + 0]);
-        part[5 * i + 1] += fma(st.c[1], faces, fma(st.c[2], edges, st.c[3] * corners));
+        kadd(acc[5 * i + 0], pc[i] * pc[i]);
+        kadd(acc[5 * i + 1], fma(st.c[1], faces, fma(st.c[2], edges, st.c[3] * corners)));
         const double ds = f - shift[i];
-        part[5 * i + 2] += ds;
-        part[5 * i + 3] = fma(ds, ds, part[5 * i + 3]);
+        kadd(acc[5 * i + 2], ds);
+        kadd(acc[5 * i + 3], ds * ds);
       }
       double V, dV[NF];
       potential<KIND, NF, double>(fc, pot, V, dV);
-      part[5 * NF] += V;
+      kadd(acc[5 * NF], V);
     }
     next();
     k0 = k1;
@@ -425,12 +427,11 @@ __global__ __launch_bounds__(kBlock) void energies27_kernel(Bufs B, const DevSca
   const double rest = (st.c[0] + 6.0 * st.c[1]) + (12.0 * st.c[2] + 8.0 * st.c[3]);
 #pragma unroll
   for (int i = 0; i < NF; ++i) {
-    const double f2 = part[5 * i + 3] + shift[i] * (2.0 * part[5 * i + 2] + shift[i] * count);
-    part[5 * i + 4] = fma(rest, f2, -part[5 * i + 1]);
+    const double m1 = acc[5 * i + 2].s + acc[5 * i + 2].c, m2 = acc[5 * i + 3].s + acc[5 * i + 3].c;
+    const double f2 = m2 + shift[i] * (2.0 * m1 + shift[i] * count);
+    acc[5 * i + 4] = KSum{-acc[5 * i + 1].s, -acc[5 * i + 1].c};
+    kadd(acc[5 * i + 4], rest * f2);
   }
-  KSum acc[NV];
-#pragma unroll
-  for (int k = 0; k < NV; ++k) acc[k] = KSum{part[k], 0.0};
   block_reduce<NV>(acc, scratch);
   if (threadIdx.x == 0) {
     double* out = partials + size_t(blockIdx.x) * 2 * NV;
