@@ -142,8 +142,8 @@ sl_status sl_lattice_create(const sl_config* cfg, void* hip_stream, sl_lattice**
  * handle zero-fills them at creation, uses them until sl_lattice_destroy and
  * never frees them; the caller keeps them alive that long and touches them
  * only between synchronising calls.  Which buffer holds the state alternates
- * with the stages (the other one is working memory: the spectra and the
- * initial states transform in it), and in FP32 storage the arrays hold each
+ * with the stages (the initial states also work in the other one; read-outs
+ * write to neither), and in FP32 storage the arrays hold each
  * field's and momentum's remainder around a homogeneous FP64 offset the
  * handle keeps: read the state with sl_get_fields.  The small buffers (partial
  * sums, scalars) are still the handle's.  SL_E_INVALID if an array is NULL,
@@ -308,8 +308,9 @@ sl_status sl_synchronize(sl_lattice* lat);
  * lattice allocates on top while it runs and frees before returning
  * (sl_set_fields / sl_get_fields staging; initial states and spectra work in
  * the field arrays that do not hold the state and allocate only where those
- * are too small, in FP32 storage of one field); 0 if invalid.  Admission keeps
- * footprint + transient free.  A lattice also holds pinned host memory for its
+ * are too small, in FP32 storage of one field, and for spectra of a lattice on
+ * the caller's arrays); 0 if invalid.  Admission keeps footprint + transient
+ * free.  A lattice also holds pinned host memory for its
  * read-backs, about 35 n bytes. */
 size_t sl_footprint_bytes(const sl_config* cfg);
 size_t sl_transient_bytes(const sl_config* cfg);

@@ -599,7 +599,8 @@ size_t spectrum_noalloc_bytes(int n, int nbins) {
 // the lattice's arrays that do not hold the state (the next stage pass
 // overwrites them), the tables and the m_eff^2 partials in the chaining
 // buffer, which is free between calls.  Nothing is allocated, except where
-// those arrays are too small: FP32 storage of one field at sides above about
+// the arrays are the caller's, which a read-out leaves as they are (spare =
+// false), and where they are too small: FP32 storage of one field at sides above about
 // 300, whose arrays are 16 n^2 bytes short and overflow into the partial-sum
 // buffer only up to there.
 struct SpecScratch {
@@ -622,8 +623,8 @@ int rows_in(const SpecScratch& S, size_t bytes, int per_row) {
   return int(std::min<size_t>(r, size_t(bin_rows_max(S.P))));
 }
 
-sl_status spec_scratch(sl_lattice* L, int nbins, int per_row, unsigned char* fixed, size_t fixed_bytes,
-                       SpecScratch& S) {
+sl_status spec_scratch(sl_lattice* L, int nbins, int per_row, bool spare, unsigned char* fixed,
+                       size_t fixed_bytes, SpecScratch& S) {
   const LatView& v = L->v;
   const int n = v.n;
   S.P = fft_plan(n);
@@ -664,7 +665,7 @@ sl_status spec_scratch(sl_lattice* L, int nbins, int per_row, unsigned char* fix
       best = q;
     }
   S.rows = rows_in(S, room, per_row);
-  if (z == n && S.rows >= want) {
+  if (spare && z == n && S.rows >= want) {
     S.B.sc = v.sc;
     S.B.z1 = zt[0];
     S.B.z2 = zt[0] + zt[1];
@@ -1059,7 +1060,7 @@ sl_status sl_init_fluctuations(sl_lattice* L, const double* phi0, const double* 
     // z, y and x passes of the inverse transform, the last one into buffer 0
     // (the scratch is buffer 1: the parity has just been reset)
     SpecScratch S;
-    sl_status st = spec_scratch(L, 1, 1, nullptr, 0, S);
+    sl_status st = spec_scratch(L, 1, 1, true, nullptr, 0, S);
     if (st != SL_OK) return st;
     HIP_TRY(launch_fft_tables(L->cfg.n, L->v.st, S.tw, S.ax, L->stream));
     for (int i = 0; i < nf; ++i) {
@@ -1366,7 +1367,7 @@ sl_status sl_spectrum(sl_lattice* L, int32_t field, int32_t nbins, double* k_out
   sl_status st = spectrum_check(L, field, nbins, k_out, p_out, count_out);
   if (st != SL_OK) return st;
   SpecScratch S;
-  st = spec_scratch(L, nbins, 3, nullptr, 0, S);
+  st = spec_scratch(L, nbins, 3, L->own_fields, nullptr, 0, S);
   if (st != SL_OK) return st;
   return spectrum_run(L, field, nbins, S, k_out, p_out, count_out);
 }
@@ -1387,7 +1388,7 @@ sl_status sl_spectrum_noalloc(sl_lattice* L, int32_t field, int32_t nbins, doubl
   // the half spectrum, then the binning partials; every kernel writes its
   // part before reading it
   SpecScratch S;
-  st = spec_scratch(L, nbins, 3, base, kNoAllocScratchBytes, S);
+  st = spec_scratch(L, nbins, 3, false, base, kNoAllocScratchBytes, S);
   if (st != SL_OK) return st;
   return spectrum_run(L, field, nbins, S, k_out, p_out, count_out);
 }
@@ -1401,7 +1402,7 @@ sl_status sl_spectra(sl_lattice* L, int32_t field, int32_t nbins, double* k_out,
   if (!k_out || !pf_out || !pe_out || !pn_out || !count_out)
     return fail(SL_E_INVALID, "output array is NULL");
   SpecScratch S;
-  st = spec_scratch(L, nbins, 7, nullptr, 0, S);  // 5 sums of the field's pass, 2 of the momentum's
+  st = spec_scratch(L, nbins, 7, L->own_fields, nullptr, 0, S);  // 5 sums of the field's pass, 2 of the momentum's
   if (st != SL_OK) return st;
   hipError_t e = launch_fft_tables(L->cfg.n, L->v.st, S.tw, S.ax, L->stream);
   if (e == hipSuccess) e = launch_meff(L->v, field, S.mpart, S.m2, L->stream);
