@@ -307,10 +307,9 @@ sl_status sl_synchronize(sl_lattice* lat);
  * sl_transient_bytes: an upper bound of what any single call on such a
  * lattice allocates on top while it runs and frees before returning
  * (sl_set_fields / sl_get_fields staging; initial states and spectra work in
- * the field arrays that do not hold the state and allocate only where those
- * are too small, in FP32 storage of one field, and for spectra of a lattice on
- * the caller's arrays); 0 if invalid.  Admission keeps footprint + transient
- * free.  A lattice also holds pinned host memory for its
+ * the field arrays that do not hold the state and allocate only for white noise
+ * of one FP32 field and for spectra of a lattice on the caller's arrays); 0 if
+ * invalid.  Admission keeps footprint + transient free.  A lattice also holds pinned host memory for its
  * read-backs, about 35 n bytes. */
 size_t sl_footprint_bytes(const sl_config* cfg);
 size_t sl_transient_bytes(const sl_config* cfg);

@@ -250,6 +250,11 @@ FftPlan fft_plan(int n) {
   return P;
 }
 
+void fft_plan_unpad(FftPlan& P) {
+  P.nhp = P.nh;
+  P.m_nhp = magic_of(P.nhp);
+}
+
 int fft_column_lines_log2(const FftPlan& P) {
   const int most = P.nt * kFftPerThread / P.n;
   int lg = 0;

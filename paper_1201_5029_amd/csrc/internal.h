@@ -292,6 +292,7 @@ struct FftPlan {
   unsigned m_n, m_nh, m_nhp, m_hy;
 };
 FftPlan fft_plan(int n);
+void fft_plan_unpad(FftPlan& P);  // rows of n/2 + 1 modes, as short as they get
 // Workgroups of an axis pass at most (a few rounds of resident ones); the
 // groups of lines are dealt out in a loop.
 constexpr int kFftGridMax = 4096;

@@ -322,10 +322,26 @@ Tile best_tile(int n, int nf, int prec, int st_kind, int vx, int pf, int tx) {
   return best;
 }
 
-size_t partial_doubles() {
+// Rows of partial bins that a spectrum's scratch has room for: a workgroup of
+// the binning pass for each CU.  (Fewer slow the pass down: spectra of 128^3 in
+// FP32 with one field and all bins took 184 us with 125 rows, 160 with 459; of
+// 300^3 1291 us with 116 and 883 with 256.)
+constexpr int kBinRows = 256;
+
+// Partial sums: the records of a pass and of the observables.  Spectra and
+// vacuum states work in the arrays that do not hold the state; in FP32 storage
+// of one field these are short of a half spectrum, and what is missing (16 n^2
+// bytes, in whole planes) and the rows of partial bins go here.
+size_t partial_doubles(const sl_config& c) {
   const size_t pass = size_t(kMaxPassBlocks) * 6;
   const size_t diag = size_t(4096) * 2 * (5 * kMaxFields + 1);
-  return pass > diag ? pass : diag;
+  size_t most = pass > diag ? pass : diag;
+  if (c.precision == SL_FP32 && c.nfields == 1) {
+    const size_t n = size_t(c.n), plane = 2 * n * (n / 2 + 1), array = n * n * n / 2;  // doubles
+    const size_t bins = size_t(kBinRows) * 7 * spectrum_bins(c.n, kMaxBins);
+    most = std::max(most, (n - 2 * (array / plane)) * plane + bins);
+  }
+  return most;
 }
 
 size_t round256(size_t b) { return (b + 255) / 256 * 256; }
@@ -335,7 +351,7 @@ size_t round256(size_t b) { return (b + 255) / 256 * 256; }
 // offsets inside one block.
 struct AuxLayout {
   size_t sc, offs, partials, sc1, offs1, partials1, sink, sums, energies, spec, total;
-  AuxLayout() {
+  explicit AuxLayout(const sl_config& c) {
     size_t o = 0;
     auto take = [&o](size_t bytes) {
       const size_t at = o;
@@ -344,7 +360,7 @@ struct AuxLayout {
     };
     sc = take(sizeof(DevScalars));
     offs = take(sizeof(double) * 2 * kMaxFields);
-    partials = take(partial_doubles() * sizeof(double));
+    partials = take(partial_doubles(c) * sizeof(double));
     // second buffers for chained passes (lattices of at most kChainMaxTiles tiles)
     sc1 = take(sizeof(DevScalars));
     offs1 = take(sizeof(double) * 2 * kMaxFields);
@@ -597,12 +613,11 @@ size_t spectrum_noalloc_bytes(int n, int nbins) {
 
 // Scratch of a spectrum call: the half spectrum and the binning partials in
 // the lattice's arrays that do not hold the state (the next stage pass
-// overwrites them), the tables and the m_eff^2 partials in the chaining
-// buffer, which is free between calls.  Nothing is allocated, except where
-// the arrays are the caller's, which a read-out leaves as they are (spare =
-// false), and where they are too small: FP32 storage of one field at sides above about
-// 300, whose arrays are 16 n^2 bytes short and overflow into the partial-sum
-// buffer only up to there.
+// overwrites them) and the partial-sum buffer, the tables and the m_eff^2
+// partials in the chaining buffer, which is free between calls.  Rows of modes
+// are padded where that leaves room (they are not in FP32 storage of one field
+// from sides of about 120).  Only where the arrays are the caller's, which a
+// read-out leaves as they are (spare = false), is memory allocated.
 struct SpecScratch {
   FftPlan P;
   ModeBuf B{};
@@ -634,9 +649,8 @@ sl_status spec_scratch(sl_lattice* L, int nbins, int per_row, bool spare, unsign
   S.ax = v.partials1 + 2 * size_t(n);
   S.mpart = S.ax + n;
   S.m2 = L->sums_dev;
-  const size_t plane = size_t(n) * S.P.nhp * sizeof(double2), need = plane * n;
-  const int want = std::min(bin_rows_max(S.P), 64);
   auto one_piece = [&](unsigned char* p, size_t bytes) {
+    const size_t need = size_t(n) * n * S.P.nhp * sizeof(double2);
     S.B.sc = nullptr;
     S.B.z1 = S.B.z2 = n;
     S.B.seg[0][0] = p;
@@ -651,21 +665,24 @@ sl_status spec_scratch(sl_lattice* L, int nbins, int per_row, bool spare, unsign
   // by plane), then the partial-sum buffer
   const size_t arr = L->n3 * v.nf * L->elem;
   const bool block = v.zs == 2 * v.nf;
-  const size_t cap[3] = {block ? 2 * arr : arr, block ? 0 : arr, partial_doubles() * sizeof(double)};
-  int zt[3], z = 0;
-  for (int q = 0; q < 3; ++q) {
-    zt[q] = int(std::min<size_t>(size_t(n - z), cap[q] / plane));
-    z += zt[q];
-  }
-  int best = 0;
-  size_t room = 0;
-  for (int q = 0; q < 3; ++q)
-    if (cap[q] - zt[q] * plane > room) {
-      room = cap[q] - zt[q] * plane;
-      best = q;
+  const size_t cap[3] = {block ? 2 * arr : arr, block ? 0 : arr, L->partials_n * sizeof(double)};
+  // lay the planes out with the plan's pitch; the partial bins go behind the
+  // planes of the piece with most room
+  auto fits = [&]() {
+    const size_t plane = size_t(n) * S.P.nhp * sizeof(double2);
+    int zt[3], z = 0, best = 0;
+    size_t room = 0;
+    for (int q = 0; q < 3; ++q) {
+      zt[q] = int(std::min<size_t>(size_t(n - z), cap[q] / plane));
+      z += zt[q];
     }
-  S.rows = rows_in(S, room, per_row);
-  if (spare && z == n && S.rows >= want) {
+    for (int q = 0; q < 3; ++q)
+      if (cap[q] - zt[q] * plane > room) {
+        room = cap[q] - zt[q] * plane;
+        best = q;
+      }
+    S.rows = rows_in(S, room, per_row);
+    if (z < n || S.rows < std::min(bin_rows_max(S.P), kBinRows)) return false;
     S.B.sc = v.sc;
     S.B.z1 = zt[0];
     S.B.z2 = zt[0] + zt[1];
@@ -675,9 +692,15 @@ sl_status spec_scratch(sl_lattice* L, int nbins, int per_row, bool spare, unsign
       S.B.seg[k][2] = v.partials;
       S.B.part[k] = reinterpret_cast<double*>(static_cast<unsigned char*>(S.B.seg[k][best]) + zt[best] * plane);
     }
-    return SL_OK;
+    return true;
+  };
+  if (spare) {
+    if (fits()) return SL_OK;
+    fft_plan_unpad(S.P);
+    if (fits()) return SL_OK;
   }
-  const size_t bytes = need + size_t(bin_rows_max(S.P)) * per_row * S.nbe * sizeof(double);
+  const size_t bytes = size_t(n) * n * S.P.nhp * sizeof(double2) +
+                       size_t(bin_rows_max(S.P)) * per_row * S.nbe * sizeof(double);
   if (hipMalloc(&S.owned, bytes) != hipSuccess) {
     S.owned = nullptr;
     return fail(SL_E_NOMEM, "cannot allocate transform scratch (%zu bytes)", bytes);
@@ -771,7 +794,7 @@ size_t sl_footprint_bytes(const sl_config* cfg) {
   if (!config_ok(cfg, &why)) return 0;
   const size_t n3 = size_t(cfg->n) * cfg->n * cfg->n;
   const size_t elem = cfg->precision == SL_FP32 ? 4 : 8;
-  return 4 * round256(n3 * cfg->nfields * elem) + AuxLayout().total;
+  return 4 * round256(n3 * cfg->nfields * elem) + AuxLayout(*cfg).total;
 }
 
 size_t sl_transient_bytes(const sl_config* cfg) {
@@ -893,7 +916,7 @@ sl_status create_impl(const sl_config* cfg, void* hip_stream, void* const* user,
   v.bg.nf = cfg->nfields;
   v.st = Stencil{{-6.0, 1.0, 0.0, 0.0}, 0, 0};
   retile_default(L);
-  L->partials_n = partial_doubles();
+  L->partials_n = partial_doubles(*cfg);
   L->a_host = cfg->a0;
 
   bool ok = true;
@@ -930,7 +953,7 @@ sl_status create_impl(const sl_config* cfg, void* hip_stream, void* const* user,
   }
   // the largest read-back: a spectra call's bins, m_eff^2 and the scalars
   L->back.reserve(sizeof(double) * (5 * size_t(spectrum_bins(cfg->n, kMaxBins)) + 1) + sizeof(DevScalars));
-  const AuxLayout aux;
+  const AuxLayout aux(*cfg);
   ok = ok && hipMalloc(&L->aux_mem, aux.total) == hipSuccess;
   if (ok) {
     char* base = static_cast<char*>(L->aux_mem);
