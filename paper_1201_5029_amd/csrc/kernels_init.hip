@@ -186,7 +186,10 @@ hipError_t launch_vacuum_columns(const LatView& v, int field, double m2eff, doub
                                  const double* ax, hipStream_t s) {
   VacArgs A;
   A.m2eff = m2eff;
-  A.half_amp2 = amp * amp / (2.0 * v.bg.L * v.bg.L * v.bg.L);
+  // in extended precision: L^3 alone leaves the range of doubles for sides whose
+  // modes are ordinary numbers
+  const long double L1 = v.bg.L;
+  A.half_amp2 = double(0.5L * amp * amp / (L1 * L1 * L1));
   A.inv_dx2 = v.bg.inv_dx2;
   A.seed = seed;
   A.field = field;
