@@ -342,8 +342,8 @@ hipError_t launch_vacuum_columns(const LatView& v, int field, double m2eff, doub
 int spectrum_bins(int n, int nbins);
 int bin_rows_max(const FftPlan& P);  // most rows of partial bins a pass writes
 // m_eff^2 = lattice mean of d^2V/dphi_field^2 at the synchronised fields into
-// *m2_dev (part: meff_partial_doubles() doubles of scratch).
-size_t meff_partial_doubles();
+// *m2_dev (part: 2 kMeffBlocks doubles of scratch).
+constexpr int kMeffBlocks = 1024;
 hipError_t launch_meff(const LatView& v, int field, double* part, double* m2_dev, hipStream_t s);
 // z pass and shell sums of |F|^2 / n^6; out3 = [k | P | count], nbe each.
 // `rows` workgroups, each writing 3 nbe partial sums.

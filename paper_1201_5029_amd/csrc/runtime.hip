@@ -644,7 +644,7 @@ sl_status spec_scratch(sl_lattice* L, int nbins, int per_row, bool spare, unsign
   const int n = v.n;
   S.P = fft_plan(n);
   S.nbe = spectrum_bins(n, nbins);
-  static_assert(kChainMaxTiles * 6 >= 3 * 1024 + 2 * 1024, "tables and m_eff^2 partials");
+  static_assert(kChainMaxTiles * 6 >= 3 * 1024 + 2 * kMeffBlocks, "tables and m_eff^2 partials");
   S.tw = reinterpret_cast<double2*>(v.partials1);
   S.ax = v.partials1 + 2 * size_t(n);
   S.mpart = S.ax + n;

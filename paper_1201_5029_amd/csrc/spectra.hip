@@ -48,8 +48,6 @@ __device__ __forceinline__ bool d2v_reads(int field, int i) {
   return true;
 }
 
-constexpr int kMeffBlocks = 1024;
-
 struct Bufs4 {
   const void* phi[2];
   const void* pi[2];
@@ -387,13 +385,15 @@ int spectrum_bins(int n, int nbins) {
 }
 
 int bin_rows_max(const FftPlan& P) {
-  // three 256-thread (two 512-thread) workgroups per CU are resident
+  // three workgroups of 256 threads or two of 512 per CU.  With five values of
+  // all bins the LDS of sides from about 400 up leaves room for one, and the
+  // 512 run in two rounds: 256 rows took the same time at 512^3 (3435 us) and
+  // longer at 448^3 (2414 against 2292) and 640^3 (8157 and 7485), where the
+  // momentum's pass has room for two.
   const int lg = fft_column_lines_log2(P), groups = (P.n * P.nhp + (1 << lg) - 1) >> lg;
   const int most = P.nt == 256 ? 768 : 512;
   return groups < most ? groups : most;
 }
-
-size_t meff_partial_doubles() { return size_t(kMeffBlocks) * 2; }
 
 hipError_t launch_meff(const LatView& v, int field, double* part, double* m2_dev, hipStream_t s) {
   return v.prec == SL_FP32 ? meff_prec<float>(v, field, part, m2_dev, s)
