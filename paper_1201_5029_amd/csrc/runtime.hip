@@ -185,30 +185,39 @@ constexpr double kCachedState = 270e6;
 constexpr double kSmallState = 12e6;
 
 // Lane shape for side n: sites per lane and pass mode.  Measured over sides
-// 16 .. 512, both precisions, every mode, each in its best tile (us per stage):
-//  - two sites per lane where rows divide, from side 40 up (32^3: one site 4.92,
-//    two 5.53; 40^3 5.68 and 5.52), four where a lane would otherwise move 8
-//    bytes per array (FP32, one field: 56^3 5.05 against 5.23, 128^3 9.95 against
-//    10.98; 48^3 4.95 against 4.79) or where FP32 streams from memory (256^3: 102
-//    against 113);
-//  - in the cache mode 2 (96^3 one field FP64 8.75, mode 1 9.37), but with 16
+// 16 .. 512, both precisions, every mode, each in its best tile (us per stage;
+// the whole table is profiles/default_shape_sweep.md):
+//  - two sites per lane where rows divide, from side 40 up (32^3: one site 4.86,
+//    two 5.30; 40^3 5.63 and 5.50), four where a lane would otherwise move 8
+//    bytes per array (FP32, one field: 56^3 5.03 against 5.20, 128^3 9.94 against
+//    10.95; 48^3 4.96 against 4.76) or where FP32 streams from memory (256^3: 101
+//    against 116);
+//  - in the cache mode 2 (96^3 one field FP64 8.71, mode 1 9.31), but with 16
 //    bytes per site and array, where the deeper pipeline's prologue costs more
-//    than it hides, mode 1 (150^3 38.2, mode 2 40.3; 96^3 13.9 and 14.8; 128^3
-//    level).  Non-temporal stores lose a quarter (128^3 FP64 34 against 26 us),
-//    except in a small state: 48^3 mode 5 5.8, mode 1 5.8, mode 2 6.4, and with
-//    three lattices at a time 2.7, 2.9 and 3.5 each; 64^3 6.7, 7.1, 7.9 alone but
-//    4.5, 4.3, 4.7 of three; 72^3 7.9, 8.5, 9.7 and 6.1, 5.5, 5.8;
+//    than it hides, mode 1 (144^3 32.7, mode 2 35.1; 96^3 13.9 and 14.8; 128^3
+//    level at 24.6, one site with mode 2 24.3).  Non-temporal stores lose a
+//    quarter (128^3 FP64 32 against 24.6), except in a small state: 48^3 mode 5 5.7,
+//    mode 1 5.8, mode 2 6.3, and with three lattices at a time 2.7, 2.9 and 3.5
+//    each; 64^3 6.8, 7.1, 7.8 alone but 4.5, 4.3, 4.7 of three; 72^3 7.8, 8.4, 9.5
+//    and 6.1, 5.5, 5.8;
 //  - a state that streams is written around the caches and read ahead, three
-//    planes in FP64 (mode 7; 200^3 104 us, mode 2 at best 109, mode 5 115;
-//    400^3 872 and 879), two in FP32 (mode 6; 512^3 Q-ball 821 us, mode 7 861,
-//    mode 2 1042; 256^3 104, mode 7 102) -- unless FP32 rows are no multiple
-//    of a 128-byte line, which non-temporal stores then write in parts (300^3
-//    209 us with mode 2, 220 with mode 7; 350^3 369 and 380);
-//  - the 27-point pass: two sites per lane where it streams (non-temporal, 256^3
-//    FP64 203 against 211 us) and with one field (FP64 48^3 5.91 against 6.24,
+//    planes in FP64 (mode 7; 200^3 103 us, mode 5 113; 400^3 870 and 878; 320^3
+//    423 and 434; but 256^3 193 and 191, 288^3 325 and 310, and there four sites
+//    with mode 6 299), two in FP32 (mode 6; 224^3 78.1, modes 5 and 7 78.4 and
+//    80.1; 256^3 103, 113 and 101; 384^3 378, 399 and 375; 512^3 Q-ball 818, 799
+//    and 842, mode 2 830) -- unless FP32 rows are no multiple of a 128-byte line,
+//    which non-temporal stores then write in parts (300^3 207 us with mode 2, 215
+//    with mode 6);
+//  - the 27-point pass: two sites per lane where it streams (256^3 FP64 with two
+//    fields 204 us, one site 245) and with one field (FP64 48^3 5.91 against 6.24,
 //    128^3 15.6 against 16.5, 96^3 11.1 against 10.8); in the cache one site with
-//    two fields (FP64 64^3 9.48 against 10.56, 144^3 38.2 against 40.3; FP32 96^3
-//    12.9 against 14.3), in FP32 up to side 112 (128^3 20.1 against 19.2).
+//    two fields (FP64 64^3 9.48 against 10.1, 144^3 37.6 against 40.4; FP32 96^3
+//    12.9 against 13.3), in FP32 up to side 112 (128^3 20.1 against 19.2).  A
+//    streaming state is written around the caches (256^3 FP64 202 against 210) with
+//    one field, and with two where n is a multiple of 32: stores of other rows
+//    leave lines in parts that two workgroups write (in the shapes picked 176^3 146
+//    us against 94 through the caches, 190^3 180 and 110, 208^3 254 and 153, 220^3
+//    276 and 170, 272^3 396 and 311; 240^3 alone 195 and 201).
 void lane_shape(int n, int prec, int nf, int st_kind, int* vx, int* pf) {
   const int elem = prec == SL_FP32 ? 4 : 8, site = elem * nf;
   const double state = 4.0 * site * double(n) * n * n;
@@ -216,7 +225,7 @@ void lane_shape(int n, int prec, int nf, int st_kind, int* vx, int* pf) {
   *vx = (nf <= 2 && n % 2 == 0 && n >= 40) ? 2 : 1;
   if (st_kind != 0) {
     if (!streams && nf == 2 && (elem == 8 || n < 112)) *vx = 1;
-    *pf = streams && *vx == 2 ? (1 | kPfNontemporal) : 1;
+    *pf = streams && *vx == 2 && (nf == 1 || n % 32 == 0) ? (1 | kPfNontemporal) : 1;
     return;
   }
   *pf = nf <= 2 ? 2 : 1;
@@ -246,8 +255,10 @@ int device_cus() {
 }
 
 // Estimated time (us, less a constant) of a pass in a tile shape, fitted to
-// measured passes of 83 lattices (sides 16 .. 512; the pick's mean distance
-// from the best of all shapes tried is 0.6 % in the cache, 2 % beyond): the CU
+// measured passes of 83 lattices.  Over 89 lattices of sides 16 .. 512 the rule
+// above and the pick are, in the mean, 0.8 % behind the best of all shapes and
+// modes tried in the cache (69 lattices, at most 11 %) and 2.9 % beyond (20, at
+// most 13 %; profiles/default_shape_sweep.md).  The CU
 // with the most tiles moves each of their planes and a prologue's worth more at
 // its share of the memory rate -- the sites read and written, a tenth of the
 // halo rows (mostly cache hits), the halo cells of a column, some bytes per row

@@ -40,7 +40,10 @@ def _recipe(model, n, precision, stencil):
     (224, "qball", "f32", None, (4, 6)), (96, "qball", "f64", None, (2, 1)),
     (200, "oscillon", "f64", None, (2, 2)), (208, "oscillon", "f64", None, (2, 7)),
     (256, "oscillon", "f32", None, (4, 2)), (288, "oscillon", "f32", None, (4, 6)),
-    (160, "preheat", "f64", "27", (1, 1)), (164, "preheat", "f64", "27", (2, 5)),
+    (160, "preheat", "f64", "27", (1, 1)), (164, "preheat", "f64", "27", (2, 1)),
+    # non-temporal 27-point stores of two fields: n a multiple of 32
+    (208, "preheat", "f64", "27", (2, 1)), (224, "preheat", "f64", "27", (2, 5)),
+    (208, "oscillon", "f64", "27", (2, 5)), (232, "preheat", "f32", "27", (2, 1)),
     (224, "preheat", "f32", "27", (2, 5)), (205, "preheat", "f32", "27", (1, 1)),
     (64, "free3", "f64", None, (1, 1)), (144, "free3", "f64", None, (1, 1)),
     (182, "free3", "f32", "27", (1, 1)),
