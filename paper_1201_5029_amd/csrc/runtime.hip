@@ -278,10 +278,19 @@ struct ShapeFit {
 };
 constexpr ShapeFit kFitCached = {{0.05, 0.9}, 54.0, 24.0, {0.59, 0.88}, 0.042, 0.63, 1.285};
 constexpr ShapeFit kFitStreams = {{0.92, 0.92}, 13.8, 80.0, {0.643, 0.643}, 0.0, 1.0, 1.1};
+// More than two fields that stream (one site per lane, one plane ahead), in the
+// 7-point and in the 27-point pass: fitted to 174 and 150 lattices of three to
+// eight fields, sides 144 .. 320, of which two fifths left out of a fit came out as
+// the others.  Distance from the best of all shapes tried 4.4 and 3.6 % in the
+// mean; with the fit above, to one and two fields, 6.8 and 4.2 %.
+constexpr ShapeFit kFitSeveral = {{1.1, 1.1}, 170.0, 140.0, {0.8, 0.8}, 0.15, 4.9, 1.06};
+constexpr ShapeFit kFitSeveral27 = {{0.98, 0.98}, 32.0, 37.0, {0.13, 0.13}, 0.15, 4.3, 1.04};
 
 double shape_cost(int n, int nf, int elem, int st_kind, const Tile& t, int cus) {
   const bool streams = 4.0 * elem * nf * double(n) * n * n > kCachedState;
-  const ShapeFit& F = streams ? kFitStreams : kFitCached;
+  const ShapeFit& F = !streams ? kFitCached
+                      : nf <= 2 ? kFitStreams
+                                : (st_kind == 0 ? kFitSeveral : kFitSeveral27);
   const int tiles = t.nblocks(), m = (tiles + cus - 1) / cus, row = (n + t.vx - 1) / t.vx;
   const int deep = pf_depth(t.pf) >= 2 ? 1 : 0, lag = st_kind != 0 && !streams ? 1 : 0;
   const double w = std::min(t.tx, row) * t.vx, rows = std::min(t.ty, n);
@@ -302,9 +311,13 @@ double shape_cost(int n, int nf, int elem, int st_kind, const Tile& t, int cus) 
 }
 
 // The cheapest z-chunk for lanes tx, or with tx = 0 the cheapest pair: powers
-// of two no wider than a row and the widths that cut a row into equal tiles.
+// of two no wider than a row and the widths that cut a row into equal tiles.  Of
+// these only whole 16 lanes, or exact parts of a row, where more than two fields
+// stream through the 7-point pass: with any, 176^3 of four FP64 fields took 223 us a
+// stage and 174 in 64 lanes, 174^3 of five FP32 fields 205 and 142.
 Tile best_tile(int n, int nf, int prec, int st_kind, int vx, int pf, int tx) {
   const int elem = prec == SL_FP32 ? 4 : 8, cus = device_cus(), row = (n + vx - 1) / vx;
+  const bool whole = nf > 2 && st_kind == 0 && 4.0 * elem * nf * double(n) * n * n > kCachedState;
   std::vector<int> txs;
   if (tx > 0) {
     txs.push_back(tx);
@@ -313,6 +326,7 @@ Tile best_tile(int n, int nf, int prec, int st_kind, int vx, int pf, int tx) {
       if (c <= row || c == 16) txs.push_back(c);
     for (int k = 1; k <= 16; ++k) {
       const int c = (row + k - 1) / k;
+      if (whole && c % 16 != 0 && row % c != 0) continue;
       if (c >= 16 && c <= 64 && std::find(txs.begin(), txs.end(), c) == txs.end()) txs.push_back(c);
     }
   }

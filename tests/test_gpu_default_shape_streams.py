@@ -65,3 +65,17 @@ def test_default_shape_equals_general(n, model, precision, stencil, lane):
     assert a.background()[1] == pytest.approx(b.background()[1], rel=1e-13 if precision == "f64" else 1e-9)
     a.close()
     b.close()
+
+
+@pytest.mark.parametrize("n,nf,precision", [
+    (176, 4, "f64"), (176, 8, "f32"), (144, 6, "f32"), (170, 3, "f64"), (174, 5, "f32"), (200, 3, "f64"),
+    (304, 5, "f32")])
+def test_widths_of_several_streaming_fields(n, nf, precision):
+    """More than two fields that stream through the 7-point pass: tiles of whole 16
+    lanes or exact parts of a row (ragged ones, as two fields have them, took up to
+    47 % longer than 64 lanes)."""
+    lat = sl.Lattice(n, nf, 32.0, precision=precision)
+    lat.set_potential("free", (1.0,) * nf)
+    say("n", n, nf, precision, lat.tile())
+    assert lat.tile()[0] % 16 == 0 or n % lat.tile()[0] == 0
+    lat.close()
