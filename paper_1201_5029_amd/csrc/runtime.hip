@@ -318,23 +318,27 @@ double shape_cost(int n, int nf, int elem, int st_kind, const Tile& t, int cus) 
 Tile best_tile(int n, int nf, int prec, int st_kind, int vx, int pf, int tx) {
   const int elem = prec == SL_FP32 ? 4 : 8, cus = device_cus(), row = (n + vx - 1) / vx;
   const bool whole = nf > 2 && st_kind == 0 && 4.0 * elem * nf * double(n) * n * n > kCachedState;
-  std::vector<int> txs;
+  constexpr int kParts = 16;
+  int txs[kParts + 3], ntxs = 0;  // no allocation: this runs inside calls that must not throw
+  auto add = [&](int c) {
+    if (std::find(txs, txs + ntxs, c) == txs + ntxs) txs[ntxs++] = c;
+  };
   if (tx > 0) {
-    txs.push_back(tx);
+    add(tx);
   } else {
     for (int c : {64, 32, 16})
-      if (c <= row || c == 16) txs.push_back(c);
-    for (int k = 1; k <= 16; ++k) {
+      if (c <= row || c == 16) add(c);
+    for (int k = 1; k <= kParts; ++k) {
       const int c = (row + k - 1) / k;
       if (whole && c % 16 != 0 && row % c != 0) continue;
-      if (c >= 16 && c <= 64 && std::find(txs.begin(), txs.end(), c) == txs.end()) txs.push_back(c);
+      if (c >= 16 && c <= 64) add(c);
     }
   }
   Tile best{};
   double best_us = 1e300;
-  for (int c : txs)
+  for (int q = 0; q < ntxs; ++q)
     for (int nz = 1; nz <= n; ++nz) {
-      const int tz = (n + nz - 1) / nz;
+      const int c = txs[q], tz = (n + nz - 1) / nz;
       if ((n + tz - 1) / tz != nz) continue;
       const Tile t = tile_geometry(n, c, vx, tz, pf);
       if (long(t.nblocks()) > kMaxPassBlocks) break;
