@@ -53,8 +53,10 @@ constexpr int nsums() { return 5 * NF + 1; }
 // 138 and 92 us (about 23 us of each is the launches and the wait; before, 40),
 // and 1025 -> 803 us at 512^3 q-ball.
 // The loads run two planes ahead of the arithmetic, in two register sets used
-// in turn.  A lane adds its sites' terms plainly over the chunk and the lanes'
-// and tiles' totals are combined with compensation.
+// in turn.  A lane adds each of its sites' terms plainly over the chunk, and the
+// sites', lanes' and tiles' totals are combined with compensation (both sites in
+// one sum were 2.6e-14 of the total off at 512^3, where one site's are 5e-16; the
+// second set of sums costs no time).
 constexpr int kEX = 64, kEY = kBlock / kEX;
 
 template <typename T, int VX>
@@ -137,9 +139,11 @@ __global__ __launch_bounds__(kBlock) void energies7_kernel(Bufs B, const DevScal
   }
 
   auto wrapz = [n](int zz) { return zz >= n ? zz - n : zz; };
-  double part[NV];
+  double part[VX][NV];  // of the lane's first and second sites
 #pragma unroll
-  for (int k = 0; k < NV; ++k) part[k] = 0.0;
+  for (int v = 0; v < VX; ++v)
+#pragma unroll
+    for (int k = 0; k < NV; ++k) part[v][k] = 0.0;
   // drifted field at z, z+1 and momenta at z of the own sites; drifted halo
   // of plane z
   double fc[NF][VX], fp[NF][VX], pc[NF][VX], pp[NF][VX], hc[NF][VX];
@@ -231,16 +235,16 @@ __global__ __launch_bounds__(kBlock) void energies7_kernel(Bufs B, const DevScal
           const double fcv = fc[i][v];
           const double dx = (v + 1 < VX ? fc[i][v + 1 < VX ? v + 1 : v] : L[1]) - fcv;
           const double dy = L[LW] - fcv, dz = fp[i][v] - fcv;
-          part[5 * i + 0] = fma(pc[i][v], pc[i][v], part[5 * i + 0]);
-          part[5 * i + 1] += fma(dx, dx, fma(dy, dy, dz * dz));
+          part[v][5 * i + 0] = fma(pc[i][v], pc[i][v], part[v][5 * i + 0]);
+          part[v][5 * i + 1] += fma(dx, dx, fma(dy, dy, dz * dz));
           const double ds = fcv - shift[i];
-          part[5 * i + 2] += ds;
-          part[5 * i + 3] = fma(ds, ds, part[5 * i + 3]);
+          part[v][5 * i + 2] += ds;
+          part[v][5 * i + 3] = fma(ds, ds, part[v][5 * i + 3]);
           f[i] = fcv;
         }
         double V, dV[NF];
         potential<KIND, NF, double>(f, pot, V, dV);
-        part[5 * NF] += V;
+        part[v][5 * NF] += V;
       }
     }
     shift_planes();
@@ -254,10 +258,16 @@ __global__ __launch_bounds__(kBlock) void energies7_kernel(Bufs B, const DevScal
   }
   if (z < zend) plane(Half<0>{}, z);
 #pragma unroll
-  for (int i = 0; i < NF; ++i) part[5 * i + 4] = -part[5 * i + 1];
+  for (int v = 0; v < VX; ++v)
+#pragma unroll
+    for (int i = 0; i < NF; ++i) part[v][5 * i + 4] = -part[v][5 * i + 1];
   KSum acc[NV];
 #pragma unroll
-  for (int k = 0; k < NV; ++k) acc[k] = KSum{part[k], 0.0};
+  for (int k = 0; k < NV; ++k) {
+    acc[k] = KSum{part[0][k], 0.0};
+#pragma unroll
+    for (int v = 1; v < VX; ++v) kadd(acc[k], part[v][k]);
+  }
   block_reduce<NV>(acc, scratch);
   if (threadIdx.x == 0) {
     double* out = partials + size_t(blockIdx.x) * 2 * NV;

@@ -1,4 +1,4 @@
-"""Rounding of the general-stencil observables' sums over long chunks: a
+"""Rounding of the observables' sums over long chunks, with a general stencil: a
 homogeneous state, whose lattice sums are its values, at a side where a lane
 adds 128 planes.  Every lane then rounds alike, so that a plain sum's error
 (1e-15 to 3e-15 of the total for these values, found on the CPU) is not averaged
@@ -41,4 +41,22 @@ def test_sums_of_a_long_chunk(p):
     assert e["pot"] == pytest.approx(want, rel=5e-16, abs=0.0)
     assert e["mean"][0] == p and e["var"][0] == 0.0 and e["grad"][0] == 0.0
     assert math.isfinite(e["rho"])
+    lat.close()
+
+
+@pytest.mark.parametrize("p", (0.8868600418849901, 0.4873891512036095, 0.6978830298032184))
+def test_sites_of_a_lane_are_summed_apart(p):
+    """The 7-point walk adds a lane's terms plainly over its chunk, 512 planes at
+    this side: one site's worth, not those of both sites of a lane, whose 1024
+    terms are 2e-14 to 3e-14 off for these values where 512 are less than 4e-15."""
+    n = 512
+    one, both = abs(_plain_error(p, n)), abs(_plain_error(p, 2 * n))
+    lat = sl.Lattice(n, 1, 64.0, expand=False)
+    lat.set_potential("free", (1.0,))
+    lat.init_fluctuations((0.5,), (p,), "none")
+    kin = lat.energies()["kin"][0]
+    want = float(Fraction(p) * Fraction(p) / 2)
+    say("p", p, "plain errors", one, both, "kin", kin / want - 1)
+    assert both > one + 1.5e-14
+    assert kin == pytest.approx(want, rel=one + 5e-16, abs=0.0)
     lat.close()
